@@ -179,8 +179,8 @@ double time_plane(cps_handle* h, int l, T* b, T* x, int rb, int tb, int reps)
 
 // The plane smoother's launch shapes of every smoothed level: rings per
 // block of the transforms (the largest that fits, half and a quarter of it)
-// and r-steps in flight per lane of the elimination (4, 8, 16).  Neither
-// changes any arithmetic: a tuned solve gives the same bits.  Cached under
+// and, for lines too long for the chunked elimination, r-steps in flight per
+// lane (4, 8, 16).  Neither changes any arithmetic: a tuned solve gives the same bits.  Cached under
 // "plane/<precision>/<stencil>/<dims>" as 100 rb + tb.
 template <typename T>
 void autotune_plane(cps_handle* h, int mode)
@@ -222,7 +222,8 @@ void autotune_plane(cps_handle* h, int mode)
             const double t = time_plane<T>(h, l, b, x, rb, kTriBatch, 5);
             if (t < tbest) tbest = t, best_rb = rb;
         }
-        for (int tb : {4, 16}) {
+        for (int tb : {4, 16}) { // the streaming elimination's (plane.hpp)
+            if (tri_chunked(g)) break;
             const double t = time_plane<T>(h, l, b, x, best_rb, tb, 5);
             if (t < tbest) tbest = t, best_tb = tb;
         }

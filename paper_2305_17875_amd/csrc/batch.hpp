@@ -36,20 +36,28 @@ __global__ void __launch_bounds__(kBlock) kb_plane_fwd(const BItem* __restrict__
                                           d.ptw, d.ptwN, d.pS, d.prb);
 }
 
-template <bool CROSS>
-__global__ void __launch_bounds__(kBlock) kb_plane_tri(const BItem* __restrict__ items,
-                                                       const int* __restrict__ active,
-                                                       const PDesc<float>* __restrict__ pd,
-                                                       int level, int parity)
+// One block size for every problem: the elimination's groups of lines per
+// block follow each problem's n_r, lines too long for its chunked form take
+// the streaming one with the default r-steps in flight (the depth schedules
+// the same arithmetic, so the bits equal the single solve's).
+__global__ void __launch_bounds__(64 * kTriWaves) kb_plane_tri(const BItem* __restrict__ items,
+                                                               const int* __restrict__ active,
+                                                               const PDesc<float>* __restrict__ pd,
+                                                               int level, int parity)
 {
     CPS_BATCH_BLOCK
+    __shared__ TriLds<float> sh;
     const LDesc<float>& d = pd[it.prob].lv[level];
-    // the default r-steps in flight: one depth per launch keeps the
-    // kernel's registers those of that depth (the depth schedules the same
-    // arithmetic, so the bits equal the single solve's with its tuned one)
-    d_plane_tri<float, CROSS>((long long)bk.L * blockDim.x + threadIdx.x, d.g, d.G, d.gk,
-                              parity, d.ppiv + plane_pivot_offset(d.g, parity),
-                              reinterpret_cast<float*>(d.pS));
+    const TriTab<float> tab = tri_tab<float>(
+        d.g, parity, const_cast<float*>(d.ppiv + plane_pivot_offset(d.g, parity)));
+    float* S = reinterpret_cast<float*>(d.pS);
+    const TriLaunch tl = tri_launch(d.g, parity, kTriWaves);
+    if (!tri_chunked(d.g))
+        d_tri_stream<float>((long long)bk.L * blockDim.x + threadIdx.x, d.g, parity, tab, S);
+    else if (d.g.nh >= 32)
+        d_tri_chunk<float, true>(bk.L, tl, d.g, parity, tab, S, sh);
+    else
+        d_tri_chunk<float, false>(bk.L, tl, d.g, parity, tab, S, sh);
 }
 
 __global__ void __launch_bounds__(kBlock) kb_plane_inv(const BItem* __restrict__ items,
@@ -171,8 +179,7 @@ void b_smooth(cps_batch* B, BatchGroup& G, int l, bool reverse, bool from_zero)
                 const int parity = reverse ? 1 - k : k;
                 blaunch(B, G.pfwd[l][parity], cross ? kb_plane_fwd<true> : kb_plane_fwd<false>, l,
                         parity);
-                blaunch(B, G.ptri[l][parity], cross ? kb_plane_tri<true> : kb_plane_tri<false>, l,
-                        parity);
+                blaunch_n(B, G.ptri[l][parity], 64 * kTriWaves, kb_plane_tri, l, parity);
                 blaunch(B, G.pfwd[l][parity], kb_plane_inv, l, parity);
             }
         return;
@@ -397,7 +404,9 @@ void build_group_tables(cps_batch* B, BatchGroup& G)
                     const Geo& g = h->lv[l].geo;
                     const PlaneLaunch pl = plane_launch(g, k, h->lv[l].plane_rb);
                     pf.push_back({p, pl.blocks});
-                    pt.push_back({p, cdiv(2LL * pl.rows * (g.nh + 1), kBlock)});
+                    const TriLaunch tl = tri_launch(g, k, kTriWaves);
+                    pt.push_back({p, tri_chunked(g) ? (int)tl.blocks
+                                                    : (int)cdiv(tl.lanes, 64 * kTriWaves)});
                 }
                 build_items(G.pfwd[l][k], pf);
                 build_items(G.ptri[l][k], pt);

@@ -186,7 +186,7 @@ struct LevelMem {
     // n_phi) (m <= nh) as (re, im) pairs, and the symbols 2 cos(2 pi m/n_phi) - 2
     Buf<double> tw64, twN64, lam64;
     Buf<float> tw32, twN32, lam32;
-    // inverse pivots of the r-line eliminations of both parities (plane.hpp)
+    // tables of the r-line eliminations of both parities (plane.hpp)
     Buf<double> pv64;
     Buf<float> pv32;
 };
@@ -434,17 +434,22 @@ void plane_half_sweep_t(cps_handle* h, int l, int parity, const T* b, T* x)
         k_plane_fwd<T, kPlaneLds, CROSS><<<pl.blocks, pl.threads, 0, h->stream>>>(
             L.g, L.G, L.gk, b, x, parity, tw, twN, S, rb);
     LAUNCH_CHECK();
-    const long long lanes = 2LL * pl.rows * (L.g.nh + 1);
-    const unsigned tblocks = (unsigned)cdiv(lanes, kTriBlock);
     const T* piv = PB::piv(m) + plane_pivot_offset(L.g, parity);
-    auto tri = [&](auto TB) {
-        k_plane_tri<T, CROSS, decltype(TB)::value><<<tblocks, kTriBlock, 0, h->stream>>>(
-            L.g, L.G, L.gk, parity, piv, PB::S(h));
-    };
-    switch (tri_batch_of(m.plane_tb)) {
-    case 4: tri(IM<4>{}); break;
-    case 16: tri(IM<16>{}); break;
-    default: tri(IM<kTriBatch>{}); break;
+    const TriLaunch tl = tri_launch(L.g, parity);
+    if (tri_chunked(L.g)) {
+        auto kt = L.g.nh >= 32 ? k_plane_tri<T, true> : k_plane_tri<T, false>;
+        kt<<<tl.blocks, tl.threads, 0, h->stream>>>(L.g, parity, piv, PB::S(h));
+    } else {
+        auto tri = [&](auto TB) {
+            k_plane_tri_stream<T, decltype(TB)::value>
+                <<<(unsigned)cdiv(tl.lanes, kTriBlock), kTriBlock, 0, h->stream>>>(L.g, parity, piv,
+                                                                                   PB::S(h));
+        };
+        switch (tri_batch_of(m.plane_tb)) {
+        case 4: tri(IM<4>{}); break;
+        case 16: tri(IM<16>{}); break;
+        default: tri(IM<kTriBatch>{}); break;
+        }
     }
     LAUNCH_CHECK();
     if (L.g.nh <= kSmallRing)
@@ -1220,10 +1225,10 @@ void setup_plane(cps_handle* h)
         };
         up64(m.tw64, tw); up64(m.twN64, twN); up64(m.lam64, lam);
         if (mixed) { up32(m.tw32, tw); up32(m.twN32, twN); up32(m.lam32, lam); }
-        spec = std::max(spec, (size_t)m.nr * ((m.nt + 1) / 2) * (nh + 1));
-        // pivots of both parities, in the precision of the cycles (FP64 for
-        // the FP64 hierarchy and its per-step entry points)
-        const size_t npiv = (size_t)m.nr * m.nt * (nh + 1);
+        spec = std::max(spec, (size_t)m.nr * ((m.nt + 1) / 2) * nh);
+        // elimination tables of both parities, in the precision of the cycles
+        // (FP64 for the FP64 hierarchy and its per-step entry points)
+        const size_t npiv = (size_t)plane_pivots(m.geo);
         if (mixed) m.pv32.alloc(npiv);
         else m.pv64.alloc(npiv);
     }

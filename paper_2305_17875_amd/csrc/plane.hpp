@@ -21,12 +21,16 @@
 //    a ring lie in one wavefront, so the stages need no block barrier;
 //  - k_plane_tri: forward elimination and back substitution down and up the
 //    r-line of every (row, mode), real and imaginary parts on two lanes.  The
-//    inverse pivots depend on the operator only and are computed once per
-//    set-up (k_plane_factor); a pass streams the spectra and the pivots with
-//    a batch of r-steps in flight per lane;
+//    inverse pivots and the off-diagonals depend on the operator only and
+//    are computed once per set-up (k_plane_factor).  An r-line is split over
+//    the wavefronts of a block, 16 cells each in registers, so the spectra
+//    and the pivots cross memory once and the serial chain is 16 steps long
+//    instead of n_r;
 //  - k_plane_inv: the inverse transform back into the rows.
 // Spectra and pivots are laid out [a][row][mode], so the r-line solves read
-// and write consecutive modes across a wavefront.
+// and write consecutive modes across a wavefront.  The modes 0 and n_phi / 2
+// of a real ring are real: they share slot 0 (real and imaginary part), so
+// a ring's spectrum is n_phi reals, whole wavefronts and aligned rows.
 //
 // CROSS: the r-theta cross metrics of an axisymmetric map with cross terms
 // (the oblate shell; G_r.phi = G_theta.phi = 0, so phi still decouples).  The
@@ -175,14 +179,43 @@ __host__ __device__ inline PlaneLaunch plane_launch(const Geo& g, int parity, in
     return p;
 }
 
-// offset of parity k's pivots in a level's table
+// The elimination's tables of one parity, in one array of nr rows (nh + 3)
+// values: inverse pivots P[a][row][mode <= nh], and the r-line's sub- and
+// super-diagonal off[a][row].
+template <typename T>
+struct TriTab {
+    T* P;
+    Vec2<T>* off;
+};
+
+template <typename T>
+__host__ __device__ inline TriTab<T> tri_tab(const Geo& g, int parity, T* base)
+{
+    const long long n = (long long)g.nr * ((g.nt - parity + 1) / 2);
+    TriTab<T> t;
+    t.off = reinterpret_cast<Vec2<T>*>(base); // first: its pairs stay aligned
+    t.P = base + 2 * n;
+    return t;
+}
+
+// values of n rings' tables, rounded up to whole pairs
+__host__ __device__ inline long long plane_pivots_of(long long n, int nh)
+{
+    return (n * (nh + 3) + 1) & ~1LL;
+}
+// values of a level's tables (both parities), and where parity k's begin
+__host__ __device__ inline long long plane_pivots(const Geo& g)
+{
+    return plane_pivots_of((long long)g.nr * ((g.nt + 1) / 2), g.nh) +
+           plane_pivots_of((long long)g.nr * (g.nt / 2), g.nh);
+}
 __host__ __device__ inline long long plane_pivot_offset(const Geo& g, int parity)
 {
-    return parity ? (long long)g.nr * ((g.nt + 1) / 2) * (g.nh + 1) : 0;
+    return parity ? plane_pivots_of((long long)g.nr * ((g.nt + 1) / 2), g.nh) : 0;
 }
 
 // Right-hand sides of the rings of parity k and their real transforms:
-// S[(a rows + bi)(nh + 1) + m], m = 0..nh.
+// S[(a rows + bi) nh + m], m < nh; slot 0 holds (mode 0, mode nh), both real.
 // The r-line of row b at a: sub x_{a-1} + (dia + G_pp lam_m) x_a + sup x_{a+1},
 // with walls (zero metrics on wall faces, mirrored reads) included.
 template <typename T, bool CROSS>
@@ -317,19 +350,19 @@ __device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>*
     if (!live) return;
     wave_fft<T, NMAX>(A, nh, tr, pl.tpr, twS, false);
     const Vec2<T>* Z = A;
-    Vec2<T>* out = S + (long long)ring * (nh + 1);
-    for (int m0 = tr; m0 <= nh; m0 += kLdBatch * pl.tpr) {
+    Vec2<T>* out = S + (long long)ring * nh;
+    for (int m0 = tr; m0 < nh; m0 += kLdBatch * pl.tpr) {
         Vec2<T> w[kLdBatch];
 #pragma unroll
         for (int u = 0; u < kLdBatch; ++u) {
             const int m = m0 + u * pl.tpr;
-            if (m <= nh) w[u] = twN[m];
+            if (m < nh) w[u] = twN[m];
         }
 #pragma unroll
         for (int u = 0; u < kLdBatch; ++u) {
             const int m = m0 + u * pl.tpr;
-            if (m <= nh) {
-                const Vec2<T> zm = Z[m == nh ? 0 : m];
+            if (m < nh) {
+                const Vec2<T> zm = Z[m];
                 const Vec2<T> zc = conjv(Z[m == 0 ? 0 : nh - m]);
                 // even part E = (zm + zc) / 2, odd part O = (zm - zc) / (2i)
                 Vec2<T> E, O;
@@ -337,7 +370,12 @@ __device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>*
                 E.y = T(0.5) * (zm.y + zc.y);
                 O.x = T(0.5) * (zm.y - zc.y);
                 O.y = -T(0.5) * (zm.x - zc.x);
-                out[m] = E + cmul(w[u], O);
+                Vec2<T> X = E + cmul(w[u], O);
+                if (m == 0) { // modes 0 and nh: E + O and E - O, both real
+                    X.x = zm.x + zm.y;
+                    X.y = zm.x - zm.y;
+                }
+                out[m] = X;
             }
         }
     }
@@ -356,50 +394,205 @@ __global__ void __launch_bounds__(kBlock) k_plane_fwd(Geo g, const T* __restrict
 }
 
 // Inverse pivots of the Thomas elimination of every (row, mode) r-line of
-// parity k: P[(a rows + bi)(nh + 1) + m] = 1 / (diag - grl c_{a-1}),
-// c_a = grh_a P_a.  One thread per (row, mode); set-up only.
+// parity k, P = 1 / (diag - sub c_{a-1}) with c_a = sup_a P_a, and the
+// off-diagonals (TriTab).  One thread per (row, mode); set-up only.
 template <typename T, bool CROSS>
 __global__ void __launch_bounds__(kBlock) k_plane_factor(Geo g, const T* __restrict__ G,
                                                          long long gk, int parity,
                                                          const T* __restrict__ lam,
-                                                         T* __restrict__ P)
+                                                         T* __restrict__ base)
 {
     const int rows = (g.nt - parity + 1) / 2;
     const int nm = g.nh + 1;
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (long long)rows * nm) return;
+    const TriTab<T> tab = tri_tab(g, parity, base);
     const int bi = (int)(t / nm), m = (int)(t - (long long)bi * nm);
     const int b = 2 * bi + parity;
     const T lm = lam[m];
-    const long long stride = (long long)rows * nm;
     T c = T(0);
     for (int a = 0; a < g.nr; ++a) {
-        const long long ci = (long long)a * g.nt + b;
+        const long long ci = (long long)a * g.nt + b, row = (long long)a * rows + bi;
         T sub, dia, sup;
         plane_row<T, CROSS>(g, G, gk, a, b, sub, dia, sup);
         const T diag = dia + G[8 * gk + ci] * lm;
         const T inv = T(1) / (diag - sub * c);
-        P[a * stride + t] = inv;
+        tab.P[row * nm + m] = inv;
+        if (m == 0) {
+            tab.off[row].x = sub;
+            tab.off[row].y = sup;
+        }
         c = sup * inv;
     }
 }
 
-// Thomas algorithm along r for every (row, mode) of parity k, in place in
-// the spectra S (read as reals: lane 2u + q takes component q of system u),
-// with the inverse pivots P of k_plane_factor; TB r-steps of loads in
-// flight per lane.
-template <typename T, bool CROSS = false, int TB = kTriBatch>
-__device__ __forceinline__ void d_plane_tri(long long u, Geo g, const T* __restrict__ G,
-                                            long long gk, int parity, const T* __restrict__ P,
-                                            T* __restrict__ S)
+// The r-line solves of every (row, mode) of parity k, in place in the spectra
+// S (read as reals: lane u of a plane's 2 rows nh), with the tables of
+// k_plane_factor.  Two forms, chosen by n_r:
+//
+// Chunked (n_r <= 256, tri_chunked): an r-line is split over nw = ceil(n_r / 16)
+// wavefronts of one block, 16 cells each in registers, every load of a thread
+// issued at once.  Each wavefront eliminates its chunk from a zero value
+// below and forms how the chunk's last value depends on that value (the
+// product of its factors -sub P); after one barrier it finds the value below
+// from the chunks before it, one fma a chunk, and eliminates once more from
+// there.  The back substitution does the same from above.  The factors are
+// below 1 in magnitude (the pivots of a diagonally dominant line), so neither
+// the products nor the carried values grow.  Bound by memory: spectra in and
+// out and the pivots once, where the streaming form below reads spectra and
+// pivots twice and waits on 2 n_r dependent steps.  Finest level of the
+// 192 x 256 x 512 shell, FP64: 56.8 us (252 MB, 4.4 TB/s) against 97.2 us
+// streaming; of the oblate 128 x 128 x 256 shell, FP32, where the streaming
+// form has 258 wavefronts in all: 8.7 against 82.6 us.  16 cells a thread
+// keep the FP64 form at 116 VGPRs (16 wavefronts a CU); lines of more than
+// 256 cells would need more than one block of 1024 threads.
+//
+// Streaming (longer lines): Thomas down and up a whole line per thread, TB
+// r-steps of loads in flight.
+constexpr int kTriChunk = 16; // r-cells a thread of the chunked form holds
+constexpr int kTriWaves = 16; // wavefronts of its largest block
+
+// (32-bit byte offsets: spectra and pivots below 4 GiB in FP64)
+__host__ __device__ inline bool tri_chunked(const Geo& g)
+{
+    return g.nr <= kTriChunk * kTriWaves &&
+           8LL * g.nr * ((g.nt + 1) / 2) * (2LL * g.nh + 2) < (1LL << 32);
+}
+
+// Blocks of the elimination: nw wavefronts a line, gpb groups of 64 lines a
+// block.  waves: the block's wavefronts (0: as many as the lines need, at
+// least four).  Neither the grouping nor the block size changes a bit.
+struct TriLaunch {
+    int nw, gpb, threads;
+    long long lanes;
+    unsigned blocks;
+};
+
+__host__ __device__ inline TriLaunch tri_launch(const Geo& g, int parity, int waves = 0)
+{
+    TriLaunch t;
+    t.lanes = 2LL * ((g.nt - parity + 1) / 2) * g.nh;
+    t.nw = tri_chunked(g) ? (g.nr + kTriChunk - 1) / kTriChunk : 1;
+    if (waves) t.gpb = waves / t.nw;
+    else if (tri_chunked(g)) t.gpb = t.nw < 4 ? 4 / t.nw : 1;
+    else t.gpb = 1;
+    t.threads = 64 * (waves ? waves : t.nw * t.gpb);
+    t.blocks = (unsigned)((t.lanes + 64 * t.gpb - 1) / (64 * t.gpb));
+    return t;
+}
+
+template <typename T>
+struct TriLds {
+    Vec2<T> f[kTriWaves][64], b[kTriWaves][64]; // a chunk's end value and its factor
+};
+
+// UNI: nh >= 32, so a wavefront's lines are of one row (its off-diagonals
+// become scalar loads).
+template <typename T, bool UNI>
+__device__ __forceinline__ void d_tri_chunk(unsigned blk, const TriLaunch& tl, const Geo& g,
+                                            int parity, const TriTab<T>& tab,
+                                            T* __restrict__ S, TriLds<T>& sh)
+{
+    constexpr int K = kTriChunk;
+    const int rows = (g.nt - parity + 1) / 2, nh = g.nh, nr = g.nr;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & 63;
+    const int grp = wv / tl.nw, c = wv - grp * tl.nw;
+    const unsigned u = (blk * (unsigned)tl.gpb + (unsigned)grp) * 64u + (unsigned)lane;
+    const bool live = grp < tl.gpb && u < (unsigned)tl.lanes;
+    const unsigned t = live ? u >> 1 : 0u; // line
+    const unsigned bl = t / (unsigned)nh, m = t - bl * (unsigned)nh;
+    const unsigned bi = UNI ? (unsigned)__builtin_amdgcn_readfirstlane((int)bl) : bl;
+    // slot 0's imaginary lane carries mode nh
+    const unsigned mp = m == 0 && (u & 1) ? (unsigned)nh : m;
+    const int a0 = c * K;
+    // byte offsets of a lane's values at plane a0, and of a plane
+    const unsigned ss = (unsigned)tl.lanes * sizeof(T), sp = (unsigned)rows * (nh + 1) * sizeof(T);
+    const unsigned so = a0 * ss + u * (unsigned)sizeof(T);
+    const unsigned po = a0 * sp + (bl * (unsigned)(nh + 1) + mp) * (unsigned)sizeof(T);
+    T d[K], f[K], e[K]; // right-hand side x pivot, -sub x pivot, -sup x pivot
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        d[k] = T(0);
+        e[k] = T(0);
+        if (a0 + k < nr && live) {
+            d[k] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(S) + (so + k * ss));
+            e[k] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(tab.P) +
+                                               (po + k * sp));
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        // a few of the per-lane pairs in flight at a time (registers)
+        if (!UNI && k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        Vec2<T> o;
+        o.x = o.y = T(0);
+        if (a0 + k < nr) o = tab.off[(unsigned)(a0 + k) * (unsigned)rows + bi];
+        d[k] *= e[k];
+        f[k] = -o.x * e[k];
+        e[k] *= -o.y;
+    }
+    T below = T(0);
+    if (tl.nw > 1) {
+        Vec2<T> v;
+        v.x = T(0);
+        v.y = T(1);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            v.x = fma_t(f[k], v.x, d[k]);
+            v.y *= f[k];
+        }
+        sh.f[wv][lane] = v;
+        __syncthreads();
+        for (int w = 0; w < c; ++w) {
+            const Vec2<T> q = sh.f[wv - c + w][lane];
+            below = fma_t(q.y, below, q.x);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        below = fma_t(f[k], below, d[k]);
+        d[k] = below;
+    }
+    T above = T(0);
+    if (tl.nw > 1) {
+        Vec2<T> v;
+        v.x = T(0);
+        v.y = T(1);
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) {
+            v.x = fma_t(e[k], v.x, d[k]);
+            v.y *= e[k];
+        }
+        sh.b[wv][lane] = v;
+        __syncthreads();
+        for (int w = tl.nw - 1; w > c; --w) {
+            const Vec2<T> q = sh.b[wv - c + w][lane];
+            above = fma_t(q.y, above, q.x);
+        }
+    }
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k) {
+        above = fma_t(e[k], above, d[k]);
+        if (a0 + k < nr && live)
+            *reinterpret_cast<T*>(reinterpret_cast<char*>(S) + (so + k * ss)) = above;
+    }
+}
+
+template <typename T, int TB = kTriBatch>
+__device__ __forceinline__ void d_tri_stream(long long u, const Geo& g, int parity,
+                                             const TriTab<T>& tab, T* __restrict__ S)
 {
     const int rows = (g.nt - parity + 1) / 2;
-    const int nm = g.nh + 1, nr = g.nr, nt = g.nt;
-    const long long sys = (long long)rows * nm; // one r-plane of spectra
-    if (u >= 2 * sys) return;
+    const int nh = g.nh, nr = g.nr;
+    const long long lanes = 2LL * rows * nh; // one r-plane of spectra
+    if (u >= lanes) return;
     const long long t = u >> 1;
-    const int q = (int)(u & 1);
-    const int b = 2 * (int)(t / nm) + parity;
+    const int bi = (int)(t / nh);
+    // slot 0's imaginary lane carries mode nh
+    const bool nyq = t == (long long)bi * nh && (u & 1);
+    const T* pb = tab.P + t + bi + (nyq ? nh : 0);
+    const long long ps = (long long)rows * (nh + 1);
     T d = T(0);
     for (int a0 = 0; a0 < nr; a0 += TB) {
         T r[TB], p[TB], gl[TB];
@@ -407,15 +600,9 @@ __device__ __forceinline__ void d_plane_tri(long long u, Geo g, const T* __restr
         for (int k = 0; k < TB; ++k) {
             const int a = a0 + k;
             if (a < nr) {
-                const long long o = a * sys + t;
-                r[k] = S[2 * o + q];
-                p[k] = P[o];
-                if (CROSS) {
-                    T dia, sup;
-                    plane_row<T, true>(g, G, gk, a, b, gl[k], dia, sup);
-                } else {
-                    gl[k] = G[(long long)a * nt + b];
-                }
+                r[k] = S[a * lanes + u];
+                p[k] = pb[a * ps];
+                gl[k] = tab.off[(long long)a * rows + bi].x;
             }
         }
 #pragma unroll
@@ -423,7 +610,7 @@ __device__ __forceinline__ void d_plane_tri(long long u, Geo g, const T* __restr
             const int a = a0 + k;
             if (a < nr) {
                 d = (r[k] - gl[k] * d) * p[k];
-                S[2 * (a * sys + t) + q] = d;
+                S[a * lanes + u] = d;
             }
         }
     }
@@ -434,15 +621,9 @@ __device__ __forceinline__ void d_plane_tri(long long u, Geo g, const T* __restr
         for (int k = 0; k < TB; ++k) {
             const int a = a0 - k;
             if (a >= 0) {
-                const long long o = a * sys + t;
-                s[k] = S[2 * o + q];
-                p[k] = P[o];
-                if (CROSS) {
-                    T sub, dia;
-                    plane_row<T, true>(g, G, gk, a, b, sub, dia, gh[k]);
-                } else {
-                    gh[k] = G[(long long)(a + 1) * nt + b];
-                }
+                s[k] = S[a * lanes + u];
+                p[k] = pb[a * ps];
+                gh[k] = tab.off[(long long)a * rows + bi].y;
             }
         }
 #pragma unroll
@@ -451,23 +632,32 @@ __device__ __forceinline__ void d_plane_tri(long long u, Geo g, const T* __restr
             if (a >= 0) {
                 const T c = gh[k] * p[k];
                 xn = s[k] - c * xn;
-                S[2 * (a * sys + t) + q] = xn;
+                S[a * lanes + u] = xn;
             }
         }
     }
 }
 
-template <typename T, bool CROSS, int TB>
-__global__ void __launch_bounds__(kTriBlock) k_plane_tri(Geo g, const T* __restrict__ G,
-                                                         long long gk, int parity,
-                                                         const T* __restrict__ P,
-                                                         T* __restrict__ S)
+template <typename T, bool UNI>
+__global__ void __launch_bounds__(64 * kTriWaves) k_plane_tri(Geo g, int parity,
+                                                              const T* __restrict__ piv,
+                                                              T* __restrict__ S)
 {
-    d_plane_tri<T, CROSS, TB>((long long)blockIdx.x * blockDim.x + threadIdx.x, g, G, gk, parity,
-                              P, S);
+    __shared__ TriLds<T> sh;
+    d_tri_chunk<T, UNI>(blockIdx.x, tri_launch(g, parity), g, parity,
+                        tri_tab<T>(g, parity, const_cast<T*>(piv)), S, sh);
 }
 
-// r-steps in flight per lane of the elimination: the candidates the
+template <typename T, int TB>
+__global__ void __launch_bounds__(kTriBlock) k_plane_tri_stream(Geo g, int parity,
+                                                                const T* __restrict__ piv,
+                                                                T* __restrict__ S)
+{
+    d_tri_stream<T, TB>((long long)blockIdx.x * blockDim.x + threadIdx.x, g, parity,
+                        tri_tab<T>(g, parity, const_cast<T*>(piv)), S);
+}
+
+// r-steps in flight per lane of the streaming elimination: the candidates the
 // autotuner times (the same arithmetic in the same order for each)
 __host__ __device__ inline int tri_batch_of(int tb) { return tb == 4 || tb == 16 ? tb : kTriBatch; }
 
@@ -488,7 +678,7 @@ __device__ __forceinline__ void d_plane_inv(unsigned blk, Vec2<T>* buf, Vec2<T>*
     const bool live = rl < pl.rb && ring < pl.rings;
     Vec2<T>* A = buf + rl * nh;
     if (live) {
-        const Vec2<T>* X = S + (long long)ring * (nh + 1);
+        const Vec2<T>* X = S + (long long)ring * nh;
         for (int m0 = tr; m0 < nh; m0 += kLdBatch * pl.tpr) {
             Vec2<T> xm[kLdBatch], xc[kLdBatch], w[kLdBatch];
 #pragma unroll
@@ -496,7 +686,7 @@ __device__ __forceinline__ void d_plane_inv(unsigned blk, Vec2<T>* buf, Vec2<T>*
                 const int m = m0 + u * pl.tpr;
                 if (m < nh) {
                     xm[u] = X[m];
-                    xc[u] = conjv(X[nh - m]);
+                    xc[u] = conjv(X[m == 0 ? 0 : nh - m]);
                     w[u] = conjv(twN[m]);
                 }
             }
@@ -514,6 +704,10 @@ __device__ __forceinline__ void d_plane_inv(unsigned blk, Vec2<T>* buf, Vec2<T>*
                     Vec2<T> z;
                     z.x = E.x - O.y;
                     z.y = E.y + O.x;
+                    if (m == 0) { // slot 0: modes 0 and nh
+                        z.x = T(0.5) * (xm[u].x + xm[u].y);
+                        z.y = T(0.5) * (xm[u].x - xm[u].y);
+                    }
                     A[m] = z;
                 }
             }

@@ -117,7 +117,7 @@ size_t estimate_bytes(const cps_grid& g, const cps_opts& o)
         s += (size_t)dims[0][0] * ((dims[0][1] + 1) / 2) * (dims[0][2] / 2 + 1) * 2 * w +
              (size_t)L * (2 * dims[0][2] + 8) * 8 * 2;
         for (int l = 0; l + 1 < L; ++l)
-            s += (size_t)dims[l][0] * dims[l][1] * (dims[l][2] / 2 + 1) * w;
+            s += (size_t)dims[l][0] * dims[l][1] * (dims[l][2] / 2 + 3) * w;
     }
     s += (2 * std::max<size_t>(n0 / kBlock + 1, kMaxGrid) + 64 + S_COUNT) * 8 +
          nc * nc * 8 * 4 + nc * kGJ * 8 * 3 + (2 * nc + 1) * 4;

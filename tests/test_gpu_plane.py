@@ -193,3 +193,39 @@ def test_automatic_smoother_in_the_service():
             assert its[2] == its[0], its
         else:
             assert 3 * its[2] <= its[0], its
+
+
+# The elimination's forms by n_r and ring length: one chunk of 16 cells that
+# is full, two with a remainder of 2, the most chunks a block holds (16), and
+# the streaming form past it; rings whose lines fill a wavefront with one
+# theta row (n_phi / 2 >= 32) and shorter ones, and a last wavefront that is
+# not full (3 rows of 8 modes).
+ELIM = [(16, 6, 16), (18, 6, 64), (34, 4, 16), (128, 4, 64), (256, 4, 32), (256, 6, 4), (258, 4, 16)]
+
+
+@pytest.mark.parametrize("map_", [MAP_IDENTITY, MAP_OBLATE], ids=["box", "oblate"])
+@pytest.mark.parametrize("shape", ELIM, ids=lambda s: "x".join(map(str, s)))
+def test_elimination_chunks_and_remainders(shape, map_):
+    """One half-sweep of each parity against the oracle's sparse LU, per entry
+    to 1e-11 relative.  The shell's gap grows with n_r (a quarter of a length
+    unit a cell), so that a plane's system stays well conditioned (theta
+    couplings within 1e4 of the radial ones): n_r eps cond ~ 256 * 2e-16 * 1e2."""
+    f = 0.1 if map_ == MAP_OBLATE else 0.0
+    g = Shell(*shape, map=map_, flattening=f, r_inner=1.5, r_outer=1.5 + 0.25 * shape[0])
+    s = cps.Solver(g, precision=0, accel=0, smoother=1, n_levels=2)
+    try:
+        G = O.face_metrics(g)
+        sm = plane.PlaneSmoother(G)
+        rng = np.random.default_rng(5)
+        b = rng.standard_normal(shape)
+        x = rng.standard_normal(shape)
+        for parity in (0, 1):
+            want = sm.half_sweep(b, x, parity)
+            xd = dev(x).flatten()
+            cps.cps_debug_plane_sweep(s.h, 0, parity, dev(b).flatten(), xd)
+            got = host(xd).reshape(shape)
+            log("elimination", map_, shape, parity, relmax(got, want))
+            assert relmax(got, want) < 1e-11, (parity, relmax(got, want))
+            x = want
+    finally:
+        s.close()
