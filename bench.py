@@ -18,11 +18,12 @@ discrete solution of the paper-scale shell and of every batch problem, and
 each form's answer is compared with it (`error_vs_oracle`).  Prints one JSON
 line.
 
-Roofline: the dominant kernel is the finest-level Gauss-Seidel colour pass.
-Its duration is measured live with HIP events recorded on the solve stream
-around each of its launches in the timed region.  `traffic` comes from
-profiles/gs_pass_config2_traffic.json (FETCH_SIZE / WRITE_SIZE counter runs,
-scaled by the same counters on a plain copy of known size) when that file
+Roofline: the dominant kernel is the finest-level way up of the V-cycle
+(prolongation and four red-black passes in one launch, k_vpost_march).  Its
+duration is measured live with HIP events recorded on the solve stream around
+each of its launches in the timed region.  `traffic` comes from
+profiles/vcycle_march_config2_traffic.json (FETCH_SIZE / WRITE_SIZE counter
+runs, scaled by the same counters on a plain copy of known size) when that file
 was taken on the current kernel source, else null.
 """
 import argparse
@@ -42,14 +43,16 @@ METRIC = "Poisson unknowns/s to 1e-10 residual, FP64 vs FP32-MG+IR; serve p50/p9
 HBM_PEAK_GBS = 8000.0
 TOL = 1e-10
 KERNEL_SRC = os.path.join(ROOT, "paper_2305_17875_amd", "csrc", "kernels.hpp")
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gs_pass_config2_traffic.json")
+MARCH_SRC = os.path.join(ROOT, "paper_2305_17875_amd", "csrc", "march.hpp")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "vcycle_march_config2_traffic.json")
 PLANE_SRC = os.path.join(ROOT, "paper_2305_17875_amd", "csrc", "plane.hpp")
 PLANE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "plane_half_sweep_config2_traffic.json")
 VCYCLE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "vcycle_config2_fp64_traffic.json")
 TILE_SRC = os.path.join(ROOT, "paper_2305_17875_amd", "csrc", "tile.hpp")
 KNAMES = ["gs_pass", "residual", "apply", "restrict", "prolong", "vcycle", "divergence",
-          "correct"]
-GS_KERNEL = "k_gs_march2<double, 0, 0>"
+          "correct", "down", "up"]
+UP_KERNEL = "k_vpost_march<double>"
+MARCH_CELLS = 1 << 20  # levels of more cells take the marching path
 
 
 def log(*a):
@@ -140,13 +143,35 @@ def vcycle_bytes(levels, word, phi_invariant=True, fused=False, red_prolong=Fals
     return int(round(total)) + nc * nc * 8 + 2 * nc * word
 
 
+def march_words():
+    """Words a cell of the two launches of a level on the marching path: down
+    (b in, red x out, coarse b out) and up (red x, e and b in, x out)."""
+    return 1.0 + 0.5 + 0.125, 0.5 + 0.125 + 1.0 + 1.0
+
+
+def vcycle_bytes_marching(levels, word):
+    """vcycle_bytes with the levels of more than MARCH_CELLS cells at the
+    bytes of their two launches (and the metrics table of each once)."""
+    whole = vcycle_bytes(levels, word, fused=True, red_prolong=True)
+    for k, lv in enumerate(levels[:-1]):
+        n = lv[0] * lv[1] * lv[2]
+        if n <= MARCH_CELLS:
+            continue
+        passes = vcycle_bytes([lv, levels[k + 1]], word, fused=True, red_prolong=True)
+        ncc = levels[k + 1][0] * levels[k + 1][1] * levels[k + 1][2]
+        passes -= ncc * ncc * 8 + 2 * ncc * word
+        whole += int(round((sum(march_words()) * n + 2 * 4 * lv[0] * lv[1]) * word)) - passes
+    return whole
+
+
 def plane_half_sweep_bytes(shape, word):
     """Algorithmic HBM bytes of one zebra half-sweep of the plane smoother
     (the theta rows of one parity), per kernel with no cross-kernel fusion:
     the forward transform reads b of the relaxed rows and x of the other
     parity and writes the spectra; the r-line elimination reads and writes
-    the spectra twice (down and up) and reads the inverse pivots twice; the
-    inverse transform reads the spectra and writes x of the relaxed rows."""
+    the spectra twice (down and up) and reads the inverse pivots twice (the
+    streaming form; the chunked one moves them once, so the rate of these
+    bytes reads higher than the memory's); the inverse transform reads the spectra and writes x of the relaxed rows."""
     nr, nt, np_ = shape
     half = nr * nt * np_ // 2
     spec = nr * (nt // 2) * (np_ // 2 + 1) * 2  # words: (n_phi/2 + 1) complex per ring
@@ -181,7 +206,8 @@ def run_form(cps, torch, g, rhs, precision, steps, warmup, smoother=0, graph_vcy
         log(f"warmup {i}: status={res.status} iterations={res.iterations} "
             f"{res.seconds * 1e3:.1f} ms")
     torch.cuda.synchronize()
-    cps.cps_profile_select(s.h, [cps.KERNEL_GS])
+    timed = [cps.KERNEL_GS] if smoother else [cps.KERNEL_UP]
+    cps.cps_profile_select(s.h, timed)
     cps.cps_profile_enable(s.h, True)
     t0 = time.perf_counter()
     iters, solve_s = [], []
@@ -195,7 +221,7 @@ def run_form(cps, torch, g, rhs, precision, steps, warmup, smoother=0, graph_vcy
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / steps
     log(f"precision={precision} smoother={smoother}: timed solves done")
-    timed_gs = cps.cps_profile_read(s.h, cps.KERNEL_GS)
+    timed_pass = cps.cps_profile_read(s.h, timed[0])
     cps.cps_profile_select(s.h, None)
     for k in range(len(KNAMES)):
         cps.cps_profile_read(s.h, k)
@@ -227,7 +253,7 @@ def run_form(cps, torch, g, rhs, precision, steps, warmup, smoother=0, graph_vcy
                 iters=iters, prof=prof, prof_steps=PROF_STEPS, vcycle_graph_us=vcycle_graph_us,
                 setup_s=setup_s, solve_ms_median=statistics.median(solve_s) * 1e3,
                 solve_ms_min=min(solve_s) * 1e3,
-                timed_gs=timed_gs)
+                timed_pass=timed_pass)
 
 
 def kernel_table(prof, steps):
@@ -252,7 +278,13 @@ def vcycle_rate(prof, levels, word, steps, graph_us=None, traffic=None):
     eager = ms / cnt * 1e-3
     t = graph_us * 1e-6 if graph_us else eager
     b = vcycle_bytes(levels, word, fused=True, red_prolong=True)
-    out = {"bytes_per_cycle": b, "avg_us": t * 1e6, "achieved_GBs": b / t / 1e9,
+    # what the cycle has to move with its large levels in two launches: the
+    # rate against the memory's peak (bytes_per_cycle counts every pass's own
+    # bytes, of which the marching path moves a part only)
+    bm = vcycle_bytes_marching(levels, word)
+    out = {"marching_bytes_per_cycle": bm, "marching_achieved_GBs": bm / t / 1e9,
+           "marching_frac_of_peak": bm / t / 1e9 / HBM_PEAK_GBS,
+           "bytes_per_cycle": b, "avg_us": t * 1e6, "achieved_GBs": b / t / 1e9,
            "frac_of_peak": b / t / 1e9 / HBM_PEAK_GBS, "cycles_per_step": cnt / steps,
            "timing": ("hipGraph replay of 10 cycles, 5 launches between events "
                       "(cps_time_vcycle)") if graph_us else "HIP events around each cycle, "
@@ -303,7 +335,7 @@ def plane_form(cps, torch, g, rhs, x64, steps, warmup, answers):
         f = run_form(cps, torch, g, rhs, precision, steps, warmup, smoother=1,
                      graph_vcycle=False)
         answers[("plane", key)] = f["host_p"]
-        hs_ms, hs_n = f["timed_gs"]  # HIP events over the timed region
+        hs_ms, hs_n = f["timed_pass"]  # HIP events over the timed region
         hs_s = hs_ms / max(hs_n, 1) * 1e-3
         hb = plane_half_sweep_bytes(g.shape, word)
         err = float(torch.linalg.norm(f["p"] - x64) / torch.linalg.norm(x64))
@@ -800,7 +832,7 @@ def vcycle_traffic():
 
 
 def traffic_for(kh):
-    """Per-launch HBM bytes of the finest-level colour pass from the counter
+    """Per-launch HBM bytes of the finest-level way up from the counter
     summary, if it was taken on this kernel source."""
     try:
         d = json.load(open(TRAFFIC_FILE))
@@ -859,12 +891,11 @@ def main():
 
     f64 = run_form(cps, torch, g, rhs, 0, a.steps, a.warmup)
     s64 = f64["solver"]
-    gs_ms, gs_n = f64["timed_gs"]  # HIP events over the timed region
-    avg_gs_s = gs_ms / max(gs_n, 1) * 1e-3
-    nterms = {2: 3, 4: 5}[s64.ncolours] if s64.phi_invariant else 9
-    gs_bytes = gs_bytes_per_launch(g.shape, s64.ncolours, 8, s64.phi_invariant, nterms)
-    achieved = gs_bytes / avg_gs_s / 1e9
-    kh = kernel_hash()
+    up_ms, up_n = f64["timed_pass"]  # HIP events over the timed region
+    avg_up_s = up_ms / up_n * 1e-3
+    up_bytes = int(round((march_words()[1] * n + 4 * g.n_r * g.n_theta) * 8))
+    achieved = up_bytes / avg_up_s / 1e9
+    kh = kernel_hash(MARCH_SRC)
     line = {
         "metric": METRIC,
         "value": n / f64["sec"],
@@ -889,9 +920,10 @@ def main():
         "rel_residual": f64["res"].rel_residual,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic_for(kh),
-                     "kernel": GS_KERNEL + " (finest-level red-black colour pass, row pairs; "
-                               "the zero-iterate first pass of a cycle is a kernel of its own)",
-                     "avg_us": avg_gs_s * 1e6, "algorithmic_bytes": gs_bytes,
+                     "kernel": UP_KERNEL + " (finest-level prolongation and four red-black "
+                               "passes in one launch; bytes: red iterate, correction and "
+                               "right-hand side in, iterate out)",
+                     "avg_us": avg_up_s * 1e6, "algorithmic_bytes": up_bytes,
                      "kernel_source_sha256_16": kh, "copy_yardstick_GBs": copy_gbs,
                      "frac_of_copy": achieved / copy_gbs if copy_gbs else None},
         "kernels_fp64": kernel_table(f64["prof"], f64["prof_steps"]),

@@ -418,7 +418,12 @@ enum {
                                 from its first to its last launch) */
     CPS_KERNEL_DIVERGENCE = 6, /* the projection step's right-hand side */
     CPS_KERNEL_CORRECT = 7,    /* the projection step's velocity correction */
-    CPS_KERNEL_CLASSES = 8
+    /* point red-black cycles on a finest level of more than 2^20 cells run in
+       two launches, each a class of its own (the classes 0, 1, 3 and 4 then
+       see no launch of the cycle): */
+    CPS_KERNEL_DOWN = 8, /* pre-smoothing from zero, red residual, restriction */
+    CPS_KERNEL_UP = 9,   /* prolongation and post-smoothing */
+    CPS_KERNEL_CLASSES = 10
 };
 /* enable != 0 starts recording (and clears earlier records). */
 cps_status cps_profile_enable(cps_handle* h, int32_t enable);

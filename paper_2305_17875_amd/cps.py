@@ -340,7 +340,7 @@ def cps_debug_vcycle(h, b, x):
 
 
 KERNEL_GS, KERNEL_RESIDUAL, KERNEL_APPLY, KERNEL_RESTRICT, KERNEL_PROLONG, KERNEL_VCYCLE, \
-    KERNEL_DIVERGENCE, KERNEL_CORRECT = range(8)
+    KERNEL_DIVERGENCE, KERNEL_CORRECT, KERNEL_DOWN, KERNEL_UP = range(10)
 
 
 def cps_profile_enable(h, enable: bool):

@@ -93,6 +93,7 @@ struct BatchGroup {
     // restriction, by ring segments (1, 2)
     ItemTable rst[kMaxLevels], rr[kMaxLevels][2];
     ItemTable tile[kMaxLevels]; // problems whose level takes the tile path: its tiles
+    ItemTable mrch[kMaxLevels]; // the marching path (march.hpp): its blocks
     ItemTable pfwd[kMaxLevels][2], ptri[kMaxLevels][2]; // plane half-sweeps by parity
     ItemTable coarse, apply, vred, elem;
     hipGraphExec_t gA = nullptr, gB = nullptr;
@@ -209,6 +210,7 @@ void b_vcycle(cps_batch* B, BatchGroup& G)
     for (int l = 0; l + 1 < G.Lmax; ++l) {
         // problems whose level l takes the tile path (as vcycle() does)
         blaunch_tile(B, G.tile[l], kb_vpre_tile<float>, l);
+        blaunch_n(B, G.mrch[l], kMThreads, kb_vpre_march<float>, l);
         if (!G.gs[l].count) continue;
         b_smooth(B, G, l, false, true);
         // as vcycle(): after point red-black smoothing, the red residual on
@@ -225,6 +227,7 @@ void b_vcycle(cps_batch* B, BatchGroup& G)
     blaunch(B, G.coarse, kb_coarse<float>);
     for (int l = G.Lmax - 2; l >= 0; --l) {
         blaunch_tile(B, G.tile[l], kb_vpost_tile<float>, l);
+        blaunch_n(B, G.mrch[l], kMThreads, kb_vpost_march<float>, l);
         if (!G.gs[l].count) continue;
         // point red-black post-smoothing starts with the black pass: only
         // the red cells need the correction (as vcycle())
@@ -345,6 +348,8 @@ PDesc<float> make_desc(cps_handle* h)
         d.lv[l] = LDesc<float>{m.geo, m.G32.p, m.gk, m.x32.p, m.b32.p, m.r32.p, m.gs_ch};
         d.lv[l].tile = m.tile ? 1 : 0;
         d.lv[l].xt = m.xt32.p;
+        d.lv[l].mt = m.mt32.p;
+        d.lv[l].mg = m.mg;
         if (h->opts.smoother == 1 && l + 1 < h->L) {
             d.lv[l].ptw = reinterpret_cast<const Vec2<float>*>(m.tw32.p);
             d.lv[l].ptwN = reinterpret_cast<const Vec2<float>*>(m.twN32.p);
@@ -364,13 +369,17 @@ void build_group_tables(cps_batch* B, BatchGroup& G)
     for (int p : G.probs) G.Lmax = std::max(G.Lmax, B->h[p]->L);
     const bool red = !G.plane && G.mode == MODE_ORTHO && G.axi;
     for (int l = 0; l + 1 < G.Lmax; ++l) {
-        PG gs, res, xf, fl, tl, rs, rr1, rr2;
+        PG gs, res, xf, fl, tl, mr, rs, rr1, rr2;
         for (int p : G.probs) {
             cps_handle* h = B->h[p];
             if (l + 1 >= h->L) continue;
             const Geo& g = h->lv[l].geo;
             if (h->lv[l].tile) {
                 tl.push_back({p, tile_count(g)});
+                continue;
+            }
+            if (h->lv[l].march) {
+                mr.push_back({p, h->lv[l].mg.blocks});
                 continue;
             }
             const Geo& c = h->lv[l + 1].geo;
@@ -395,6 +404,7 @@ void build_group_tables(cps_batch* B, BatchGroup& G)
         build_items(G.xfer[l], xf);
         build_items(G.fill[l], fl);
         build_items(G.tile[l], tl);
+        build_items(G.mrch[l], mr);
         if (G.plane)
             for (int k = 0; k < 2; ++k) {
                 PG pf, pt;

@@ -13,6 +13,7 @@
 #include "project.hpp"
 #include "lines.hpp"
 #include "tile.hpp"
+#include "march.hpp"
 
 #include <hip/hip_runtime.h>
 
@@ -178,6 +179,12 @@ struct LevelMem {
     bool tile = false;
     Buf<double> xt64;
     Buf<float> xt32;
+    // large levels of the point smoother (march.hpp): also two launches; the
+    // residual buffer r holds the second iterate
+    bool march = false;
+    MarchGrid mg{};
+    Buf<double> mt64;
+    Buf<float> mt32;
     int gs_ch = 0; // marching chunk of the colour pass (0 = default; autotuned)
     // plane smoother's launch shapes (0 = default; autotuned): rings per
     // block of the transforms, r-steps in flight per lane of the elimination
@@ -287,8 +294,14 @@ float* xtl<float>(cps_handle* h, int l) { return h->lv[l].xt32.p; }
 template <typename T>
 T* xfin(cps_handle* h, int l)
 {
-    return h->lv[l].tile ? xtl<T>(h, l) : xl<T>(h, l);
+    return h->lv[l].tile ? xtl<T>(h, l) : (h->lv[l].march ? rl<T>(h, l) : xl<T>(h, l));
 }
+template <typename T>
+T* mtl(cps_handle* h, int l);
+template <>
+double* mtl<double>(cps_handle* h, int l) { return h->lv[l].mt64.p; }
+template <>
+float* mtl<float>(cps_handle* h, int l) { return h->lv[l].mt32.p; }
 
 // Brackets one finest-level launch of kernel class k with two events on the
 // handle's stream (no-op unless profiling is enabled).
@@ -705,6 +718,30 @@ void vpost_tile(cps_handle* h, int l, const T* b, const T* xi, T* xo, const T* e
     LAUNCH_CHECK();
 }
 
+// The same of a large level (march.hpp): pre writes the red cells of its
+// iterate into xr, post reads them and writes xo.  dot: partial sums of b . xo
+// in h->partial; returns their number.
+template <typename T>
+void vpre_march(cps_handle* h, int l, const T* b, T* xr, T* bc)
+{
+    const LevelMem& m = h->lv[l];
+    ProfScope ps(h, CPS_KERNEL_DOWN, l);
+    k_vpre_march<T><<<m.mg.blocks, kMThreads, 0, h->stream>>>(m.geo, m.mg, mtl<T>(h, l), b, xr,
+                                                              h->lv[l + 1].geo, bc);
+    LAUNCH_CHECK();
+}
+
+template <typename T>
+long long vpost_march(cps_handle* h, int l, const T* b, const T* xr, T* xo, const T* e, bool dot)
+{
+    const LevelMem& m = h->lv[l];
+    ProfScope ps(h, CPS_KERNEL_UP, l);
+    k_vpost_march<T><<<m.mg.blocks, kMThreads, 0, h->stream>>>(
+        m.geo, m.mg, mtl<T>(h, l), b, xr, xo, h->lv[l + 1].geo, e, dot ? h->partial.p : nullptr);
+    LAUNCH_CHECK();
+    return dot ? m.mg.blocks : 0;
+}
+
 // One V(2,2) cycle with level-0 right-hand side b0 and iterate x0 (in place).
 // dot: the last level-0 passes leave partial sums of b0 . x0 in h->partial;
 // returns their number (0 when the cycle cannot provide them).
@@ -723,11 +760,18 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
     // pre-smoothing starts from zero): pre writes the scratch iterate xt and
     // post reads it and writes x0, so no block reads what another overwrote
     const bool tile0 = h->lv[0].tile && x0_zero;
+    // the same for a finest level of the marching path, whose first iterate
+    // is in the residual buffer
+    const bool march0 = h->lv[0].march && x0_zero;
     for (int l = 0; l < L - 1; ++l) {
         const T* b = l == 0 ? b0 : bl<T>(h, l);
         T* x = l == 0 ? x0 : xl<T>(h, l);
         if (l == 0 ? tile0 : h->lv[l].tile) { // smoothing, residual, restriction
             vpre_tile<T>(h, l, b, l == 0 ? xtl<T>(h, 0) : x, bl<T>(h, l + 1));
+            continue;
+        }
+        if (l == 0 ? march0 : h->lv[l].march) {
+            vpre_march<T>(h, l, b, l == 0 ? rl<T>(h, 0) : x, bl<T>(h, l + 1));
             continue;
         }
         // coarse corrections start from zero
@@ -755,6 +799,14 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
         }
         if (l > 0 && h->lv[l].tile) { // prolongation and smoothing, into xt
             vpost_tile<T>(h, l, b, x, xtl<T>(h, l), e);
+            continue;
+        }
+        if (l == 0 && march0) {
+            parts = vpost_march<T>(h, 0, b, rl<T>(h, 0), x, e, dot);
+            continue;
+        }
+        if (l > 0 && h->lv[l].march) {
+            vpost_march<T>(h, l, b, x, rl<T>(h, l), e, false);
             continue;
         }
         // point red-black post-smoothing starts with the black pass: only
@@ -981,6 +1033,22 @@ void plane_factors(cps_handle* h)
     }
 }
 
+// Metrics tables of the levels on the marching path (march.hpp); with the
+// metrics at set-up and again when they change.
+void march_tables(cps_handle* h)
+{
+    for (int l = 0; l + 1 < h->L; ++l) {
+        const LevelMem& m = h->lv[l];
+        if (!m.march) continue;
+        const unsigned blocks = nblk((long long)(m.nr + 2 * kMPad) * (m.nt / 2 + 1));
+        if (h->opts.precision == 1)
+            k_march_table<float><<<blocks, kBlock, 0, h->stream>>>(m.geo, m.G32.p, m.gk, m.mt32.p);
+        else
+            k_march_table<double><<<blocks, kBlock, 0, h->stream>>>(m.geo, m.G64.p, m.gk, m.mt64.p);
+        LAUNCH_CHECK();
+    }
+}
+
 // OR of the per-block flags a metrics kernel left in `dflags`.
 int gather_flags(cps_handle* h, const Buf<int>& dflags, long long blocks)
 {
@@ -1152,6 +1220,7 @@ int compute_operator(cps_handle* h, Buf<double>* unat = nullptr, int user_flags 
         if (hbad) fail(CPS_E_INVALID, "coarsest operator is singular");
     }
     if (h->lv[0].pv64.p || h->lv[0].pv32.p) plane_factors(h); // new metrics of a set-up hierarchy
+    march_tables(h);
     h->cm_valid = false; // the projection step's face tables follow the map
     h->lf_valid[0] = h->lf_valid[1] = false;
     return mode;
@@ -1308,11 +1377,19 @@ void build(cps_handle* h)
     // from zero, and then its dot products come from a separate reduction)
     for (int l = 0; l + 1 < h->L; ++l) {
         LevelMem& m = h->lv[l];
-        m.tile = marching(h) && h->ncol == 2 && h->opts.smoother == 0 && tile_fits(m.geo, mixed);
+        const bool point7 = marching(h) && h->ncol == 2 && h->opts.smoother == 0;
+        m.tile = point7 && tile_fits(m.geo, mixed);
+        m.march = point7 && !m.tile && march_fits(m.geo);
+        if (m.march) {
+            m.mg = march_grid(m.geo, mixed);
+            if (mixed) m.mt32.alloc(march_table_words(m.geo));
+            else m.mt64.alloc(march_table_words(m.geo));
+        }
         if (!m.tile) continue;
         if (mixed) m.xt32.alloc(m.n);
         else m.xt64.alloc(m.n);
     }
+    march_tables(h);
     autotune(h, h->opts.tune);
     HIPC(hipStreamSynchronize(h->stream));
 }
@@ -1326,6 +1403,7 @@ void destroy(cps_handle* h)
         m.G64.release(); m.G32.release();
         m.x64.release(); m.b64.release(); m.r64.release();
         m.xt64.release(); m.xt32.release();
+        m.mt64.release(); m.mt32.release();
         m.x32.release(); m.b32.release(); m.r32.release();
     }
     h->Ainv.release(); h->partial.release(); h->sc.release();
@@ -1461,12 +1539,13 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
             // formed from the FP32 correction (no FP64 cast pass, z not stored)
             const bool cast_fused = fused && mixed;
             float* r32 = cast_fused ? h->lv[0].b32.p : nullptr;
-            // FP64 point smoothing with the per-kernel finest level: the step
-            // also makes the next cycle's zero-iterate first pass, z = r / D
-            // on the red cells, and forms q = A p again from p, so the
-            // direction kernel does not store q (k_cg_step_z)
-            const bool zfused = fused && !mixed && h->opts.smoother == 0 && h->ncol == 2 &&
-                                !h->lv[0].tile;
+            // FP64: the step forms q = A p again from p, so the direction
+            // kernel does not store q (k_cg_step_z).  Point smoothing with the
+            // per-kernel finest level: it also makes the next cycle's
+            // zero-iterate first pass, z = r / D on the red cells
+            const bool qfree = fused && !mixed && h->opts.smoother == 0 && h->ncol == 2 &&
+                               !h->lv[0].tile;
+            const bool zfused = qfree && !h->lv[0].march;
             // x += alpha p, r -= alpha q and ||r||^2 (the first iteration's
             // step, and the tail of every later body; alpha comes from the
             // launch that stored p.q).  On the fused path the next direction
@@ -1474,12 +1553,11 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
             // the last update runs after the loop.
             double* plast = p; // direction of the last step
             auto step = [&](double* pk) {
-                if (zfused) { // q = A p formed again from p (the direction kernel keeps no q)
+                if (qfree) { // q = A p formed again from p (the direction kernel keeps no q)
                     const MarchShape ms = stencil_shape(g0);
-                    k_cg_step_z<<<ms.grid, kBlock, 0, h->stream>>>(g0, h->lv[0].G64.p,
-                                                                   h->lv[0].gk, ms.bpa, ms.ch,
-                                                                   h->sc.p, pk, r, z,
-                                                                   h->partial.p);
+                    auto ks = zfused ? k_cg_step_z<true> : k_cg_step_z<false>;
+                    ks<<<ms.grid, kBlock, 0, h->stream>>>(g0, h->lv[0].G64.p, h->lv[0].gk, ms.bpa,
+                                                          ms.ch, h->sc.p, pk, r, z, h->partial.p);
                     LAUNCH_CHECK();
                     reduce_norm(h, ms.grid, S_RR);
                 } else {
@@ -1529,7 +1607,7 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
                                 else
                                     kd<<<ms.grid, kBlock, 0, h->stream>>>(
                                         g0, h->lv[0].G64.p, h->lv[0].gk, ms.bpa, ms.ch, z, pc,
-                                        h->sc.p + S_BETA, pnx, zfused ? nullptr : q,
+                                        h->sc.p + S_BETA, pnx, qfree ? nullptr : q,
                                         h->partial.p, x, h->sc.p);
                                 LAUNCH_CHECK();
                             }

@@ -2417,7 +2417,8 @@ __global__ void __launch_bounds__(kBlock) k_cg_step(long long n, const double* _
 }
 
 // The FP64 CG step on a row-pair level (the iterate's update is carried by
-// the direction kernel), which also makes the next V-cycle's first pass.
+// the direction kernel); Z: it also makes the next V-cycle's first pass
+// (where the cycle's finest level runs pass by pass).
 // q is not read from memory: q = A p is formed again from the stored
 // direction p (march2_apply on the same values with the same sums as the
 // direction kernel's product, so q has the same bits), and the direction
@@ -2426,6 +2427,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_step(long long n, const double* _
 // plane a) with D and the division of the zero-iterate colour pass (the
 // same values).  The theta rows just outside a pair come from the adjacent
 // wavefronts through LDS, as in the direction kernel.
+template <bool Z>
 __global__ void __launch_bounds__(kBlock) k_cg_step_z(Geo g, const double* __restrict__ G,
                                                        long long gk, int bpa, int ch,
                                                        const double* __restrict__ sc,
@@ -2486,7 +2488,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_step_z(Geo g, const double* __res
                 st_once(r + base + o[k], v);
                 acc = __builtin_fma(v, v, acc);
                 const bool red = (k == 0 || k == 3) == even;
-                if (red) st_once(z + base + o[k], v / (k < 2 ? D0 : D1));
+                if (Z && red) st_once(z + base + o[k], v / (k < 2 ? D0 : D1));
             }
             cm = c;
             c = nb.up;
@@ -2714,6 +2716,11 @@ enum VecId {
     V_X = 0, V_B0, V_R, V_Z, V_P, V_Q, V_R0, V_V, V_S, V_T, V_PH, V_SH, V_RHS, V_OUT, V_COUNT
 };
 
+// blocks of the two-launch V-cycle of a large level (march.hpp)
+struct MarchGrid {
+    int strips, segs, own, ch, chunks, blocks;
+};
+
 template <typename T>
 struct LDesc {
     Geo g;
@@ -2733,6 +2740,10 @@ struct LDesc {
     // iterate goes to xt
     int tile;
     T* xt;
+    // large levels of the point smoother (march.hpp): the metrics table
+    // (null elsewhere) and the launch
+    const T* mt;
+    MarchGrid mg;
 };
 
 template <typename T>

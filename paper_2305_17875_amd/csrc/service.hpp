@@ -70,6 +70,7 @@ size_t handle_bytes(const cps_handle* h)
         const LevelMem& m = h->lv[l];
         add(m.G64); add(m.G32); add(m.x64); add(m.b64); add(m.r64);
         add(m.x32); add(m.b32); add(m.r32); add(m.xt64); add(m.xt32);
+        add(m.mt64); add(m.mt32);
     }
     add(h->Ainv); add(h->partial); add(h->sc);
     add(h->x0); add(h->b0); add(h->r); add(h->z); add(h->pd); add(h->q);
@@ -102,6 +103,10 @@ size_t estimate_bytes(const cps_grid& g, const cps_opts& o)
         else s += n * 8 * ((l > 0 ? 2 : 0) + (l + 1 < L ? 1 : 0));
         // the tile path's second iterate (small levels, point smoother)
         if (l + 1 < L && n <= (size_t)tile_max_cells(mixed)) s += n * (mixed ? 4 : 8);
+        // the marching path's metrics table (large levels)
+        if (l + 1 < L && n > (size_t)kMarchCells)
+            s += (size_t)march_table_words(make_geo(dims[l][0], dims[l][1], dims[l][2])) *
+                 (mixed ? 4 : 8);
     }
     const size_t n0 = (size_t)g.n_r * g.n_theta * g.n_phi;
     const size_t nc = (size_t)dims[L - 1][0] * dims[L - 1][1] * dims[L - 1][2];
