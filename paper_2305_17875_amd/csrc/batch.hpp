@@ -27,13 +27,27 @@ template <bool CROSS>
 __global__ void __launch_bounds__(kBlock) kb_plane_fwd(const BItem* __restrict__ items,
                                                        const int* __restrict__ active,
                                                        const PDesc<float>* __restrict__ pd,
-                                                       int level, int parity)
+                                                       int level, int parity, int zero)
 {
     CPS_BATCH_BLOCK
     __shared__ Vec2<float> buf[kPlaneLds], twS[kPlaneLds / 2];
     const LDesc<float>& d = pd[it.prob].lv[level];
     d_plane_fwd<float, kSmallRing, CROSS>(bk.L, buf, twS, d.g, d.G, d.gk, d.b, d.x, parity,
-                                          d.ptw, d.ptwN, d.pS, d.prb);
+                                          d.ptw, d.ptwN, d.pS, d.prb, zero != 0);
+}
+
+// half-sweeps of the levels whose rows' planes are small
+template <bool CROSS>
+__global__ void __launch_bounds__(64 * kTriWaves) kb_plane_row(const BItem* __restrict__ items,
+                                                               const int* __restrict__ active,
+                                                               const PDesc<float>* __restrict__ pd,
+                                                               int level, int parity, int zero)
+{
+    CPS_BATCH_BLOCK
+    __shared__ PlaneRowLds<float> sh;
+    const LDesc<float>& d = pd[it.prob].lv[level];
+    d_plane_row<float, CROSS>(bk.L, sh, d.g, d.G, d.gk, d.b, d.x, parity, d.ptw, d.ptwN,
+                                   d.ppiv + plane_pivot_offset(d.g, parity), zero != 0);
 }
 
 // One block size for every problem: the elimination's groups of lines per
@@ -95,6 +109,7 @@ struct BatchGroup {
     ItemTable tile[kMaxLevels]; // problems whose level takes the tile path: its tiles
     ItemTable mrch[kMaxLevels]; // the marching path (march.hpp): its blocks
     ItemTable pfwd[kMaxLevels][2], ptri[kMaxLevels][2]; // plane half-sweeps by parity
+    ItemTable prow[kMaxLevels][2]; // the one-launch ones (small planes)
     ItemTable coarse, apply, vred, elem;
     hipGraphExec_t gA = nullptr, gB = nullptr;
     hipGraph_t graphA = nullptr, graphB = nullptr;
@@ -173,13 +188,15 @@ void bdot(cps_batch* B, const ItemTable& vred, int u, int v, int slot)
 void b_smooth(cps_batch* B, BatchGroup& G, int l, bool reverse, bool from_zero)
 {
     if (G.plane) { // as smooth() with the plane smoother: two sweeps of two half-sweeps
-        if (from_zero) blaunch(B, G.fill[l], kb_fill_level<float>, l);
         const bool cross = G.mode == MODE_RT;
         for (int s = 0; s < 2; ++s)
             for (int k = 0; k < 2; ++k) {
                 const int parity = reverse ? 1 - k : k;
+                const int zero = from_zero && s == 0 && k == 0 ? 1 : 0;
+                blaunch_n(B, G.prow[l][parity], 64 * kTriWaves,
+                          cross ? kb_plane_row<true> : kb_plane_row<false>, l, parity, zero);
                 blaunch(B, G.pfwd[l][parity], cross ? kb_plane_fwd<true> : kb_plane_fwd<false>, l,
-                        parity);
+                        parity, zero);
                 blaunch_n(B, G.ptri[l][parity], 64 * kTriWaves, kb_plane_tri, l, parity);
                 blaunch(B, G.pfwd[l][parity], kb_plane_inv, l, parity);
             }
@@ -407,12 +424,16 @@ void build_group_tables(cps_batch* B, BatchGroup& G)
         build_items(G.mrch[l], mr);
         if (G.plane)
             for (int k = 0; k < 2; ++k) {
-                PG pf, pt;
+                PG pf, pt, pr;
                 for (int p : G.probs) {
                     cps_handle* h = B->h[p];
                     if (l + 1 >= h->L) continue;
                     const Geo& g = h->lv[l].geo;
                     const PlaneLaunch pl = plane_launch(g, k, h->lv[l].plane_rb);
+                    if (plane_row_fits(g)) {
+                        pr.push_back({p, pl.rows});
+                        continue;
+                    }
                     pf.push_back({p, pl.blocks});
                     const TriLaunch tl = tri_launch(g, k, kTriWaves);
                     pt.push_back({p, tri_chunked(g) ? (int)tl.blocks
@@ -420,6 +441,7 @@ void build_group_tables(cps_batch* B, BatchGroup& G)
                 }
                 build_items(G.pfwd[l][k], pf);
                 build_items(G.ptri[l][k], pt);
+                build_items(G.prow[l][k], pr);
             }
     }
     PG co, ap, vr, el;

@@ -426,8 +426,9 @@ bool plane_class_ok(const cps_handle* h)
     return h->axi && (h->mode == MODE_ORTHO || h->mode == MODE_RT);
 }
 
+// zero: the iterate is zero (it is not read).
 template <typename T, bool CROSS>
-void plane_half_sweep_t(cps_handle* h, int l, int parity, const T* b, T* x)
+void plane_half_sweep_t(cps_handle* h, int l, int parity, const T* b, T* x, bool zero)
 {
     using PB = PlaneBufs<T>;
     const Level<T> L = view<T>(h, l);
@@ -439,15 +440,22 @@ void plane_half_sweep_t(cps_handle* h, int l, int parity, const T* b, T* x)
     const auto* tw = reinterpret_cast<const Vec2<T>*>(PB::tw(m));
     const auto* twN = reinterpret_cast<const Vec2<T>*>(PB::twN(m));
     auto* S = reinterpret_cast<Vec2<T>*>(PB::S(h));
+    const T* piv = PB::piv(m) + plane_pivot_offset(L.g, parity);
+    const int z = zero ? 1 : 0;
     ProfScope ps(h, CPS_KERNEL_GS, l);
+    if (plane_row_fits(L.g)) { // the row's plane in LDS: one launch
+        k_plane_row<T, CROSS><<<pl.rows, plane_row_threads(L.g), 0, h->stream>>>(
+            L.g, L.G, L.gk, b, x, parity, tw, twN, piv, z);
+        LAUNCH_CHECK();
+        return;
+    }
     if (L.g.nh <= kSmallRing)
         k_plane_fwd<T, kSmallRing, CROSS><<<pl.blocks, pl.threads, 0, h->stream>>>(
-            L.g, L.G, L.gk, b, x, parity, tw, twN, S, rb);
+            L.g, L.G, L.gk, b, x, parity, tw, twN, S, rb, z);
     else
         k_plane_fwd<T, kPlaneLds, CROSS><<<pl.blocks, pl.threads, 0, h->stream>>>(
-            L.g, L.G, L.gk, b, x, parity, tw, twN, S, rb);
+            L.g, L.G, L.gk, b, x, parity, tw, twN, S, rb, z);
     LAUNCH_CHECK();
-    const T* piv = PB::piv(m) + plane_pivot_offset(L.g, parity);
     const TriLaunch tl = tri_launch(L.g, parity);
     if (tri_chunked(L.g)) {
         auto kt = L.g.nh >= 32 ? k_plane_tri<T, true> : k_plane_tri<T, false>;
@@ -475,15 +483,16 @@ void plane_half_sweep_t(cps_handle* h, int l, int parity, const T* b, T* x)
 }
 
 template <typename T>
-void plane_half_sweep(cps_handle* h, int l, int parity, const T* b, T* x)
+void plane_half_sweep(cps_handle* h, int l, int parity, const T* b, T* x, bool zero = false)
 {
-    if (h->mode == MODE_RT) plane_half_sweep_t<T, true>(h, l, parity, b, x);
-    else plane_half_sweep_t<T, false>(h, l, parity, b, x);
+    if (h->mode == MODE_RT) plane_half_sweep_t<T, true>(h, l, parity, b, x, zero);
+    else plane_half_sweep_t<T, false>(h, l, parity, b, x, zero);
 }
 
 // Gauss-Seidel sweeps over all colours (reverse order for post-smoothing).
-// from_zero: x is zero on entry; with two colours it is then not even read
-// (nor initialised) before the first pass writes it, otherwise it is filled.
+// from_zero: x is zero on entry; with two colours and with the plane smoother
+// it is then not even read (nor initialised) before a pass writes it,
+// otherwise it is filled.
 // With the plane smoother a sweep is the two zebra half-sweeps (parity 0
 // then 1, reversed for post-smoothing).
 // dot (two colours on marching levels): the last two passes, which leave
@@ -496,9 +505,11 @@ long long smooth(cps_handle* h, int l, const T* b, T* x, int sweeps, bool revers
                  bool from_zero = false, double* dot = nullptr, bool first_done = false)
 {
     if (h->opts.smoother == 1) {
-        if (from_zero) fill<T>(h, x, h->lv[l].n, T(0));
+        // from zero the first half-sweep reads no x, and the second only the
+        // rows that the first has written: x need not be filled
         for (int s = 0; s < sweeps; ++s)
-            for (int k = 0; k < 2; ++k) plane_half_sweep<T>(h, l, reverse ? 1 - k : k, b, x);
+            for (int k = 0; k < 2; ++k)
+                plane_half_sweep<T>(h, l, reverse ? 1 - k : k, b, x, from_zero && s == 0 && k == 0);
         return 0;
     }
     const bool skip = from_zero && h->ncol == 2;

@@ -255,33 +255,64 @@ __device__ __forceinline__ void plane_row(const Geo& g, const T* __restrict__ G,
     }
 }
 
-// Bodies take the logical block index (the batched form maps its blocks to
-// problems); buf and twS are the block's LDS.
-template <typename T, int NMAX, bool CROSS = false>
-__device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>* twS, Geo g,
-                                            const T* __restrict__ G, long long gk,
-                                            const T* __restrict__ bv, const T* __restrict__ x,
-                                            int parity, const Vec2<T>* __restrict__ tw,
-                                            const Vec2<T>* __restrict__ twN,
-                                            Vec2<T>* __restrict__ S, int rb = 0)
+// Mode m < nh of a real ring from its half-length transform Z: zm = Z[m],
+// zr = Z[nh - m] (Z[0] for m = 0), w = exp(-2 pi i m / n_phi).  Slot 0: modes 0
+// and nh.
+template <typename T>
+__device__ __forceinline__ Vec2<T> ring_mode(int m, Vec2<T> zm, Vec2<T> zr, Vec2<T> w)
 {
-    const PlaneLaunch pl = plane_launch(g, parity, rb);
+    const Vec2<T> zc = conjv(zr);
+    // even part E = (zm + zc) / 2, odd part O = (zm - zc) / (2i)
+    Vec2<T> E, O;
+    E.x = T(0.5) * (zm.x + zc.x);
+    E.y = T(0.5) * (zm.y + zc.y);
+    O.x = T(0.5) * (zm.y - zc.y);
+    O.y = -T(0.5) * (zm.x - zc.x);
+    Vec2<T> X = E + cmul(w, O);
+    if (m == 0) { // E + O and E - O, both real
+        X.x = zm.x + zm.y;
+        X.y = zm.x - zm.y;
+    }
+    return X;
+}
+
+// and back: Z[m] from xm = X[m], xr = X[nh - m] (X[0] for m = 0)
+template <typename T>
+__device__ __forceinline__ Vec2<T> ring_value(int m, Vec2<T> xm, Vec2<T> xr, Vec2<T> w)
+{
+    const Vec2<T> xc = conjv(xr);
+    // E = (xm + xc) / 2, O = (xm - xc) conj(w) / 2, Z = E + i O
+    Vec2<T> E, D;
+    E.x = T(0.5) * (xm.x + xc.x);
+    E.y = T(0.5) * (xm.y + xc.y);
+    D.x = T(0.5) * (xm.x - xc.x);
+    D.y = T(0.5) * (xm.y - xc.y);
+    const Vec2<T> O = cmul(conjv(w), D);
+    Vec2<T> z;
+    z.x = E.x - O.y;
+    z.y = E.y + O.x;
+    if (m == 0) {
+        z.x = T(0.5) * (xm.x + xm.y);
+        z.y = T(0.5) * (xm.x - xm.y);
+    }
+    return z;
+}
+
+// Right-hand side of the ring (a, b) into A: b minus the terms of rows b -/+ 1;
+// zero: the iterate is zero, so x is not read.
+template <typename T, bool CROSS>
+__device__ __forceinline__ void plane_rhs(const Geo& g, const T* __restrict__ G, long long gk,
+                                          const T* __restrict__ bv, const T* __restrict__ x, int a,
+                                          int b, int tr, int tpr, bool zero, Vec2<T>* A)
+{
     const int nh = g.nh;
-    for (int q = (int)threadIdx.x; q < nh / 2; q += pl.threads) twS[q] = tw[q];
-    const int rl = (int)threadIdx.x / pl.tpr, tr = (int)threadIdx.x - rl * pl.tpr;
-    const int ring = (int)blk * pl.rb + rl;
-    // threads past the block's rings (a batched launch of a fixed block
-    // size) only take part in the barrier
-    const bool live = rl < pl.rb && ring < pl.rings;
-    const int a = live ? ring / pl.rows : 0, bi = live ? ring - a * pl.rows : 0;
-    const int b = 2 * bi + parity;
-    Vec2<T>* A = buf + rl * nh;
-    if (live && CROSS) {
+    if constexpr (CROSS) {
         // b + sum over rows b -/+ 1 at a - 1, a, a + 1 (mirrored in r) of
         // coefficient x value: the theta-face metrics and both faces' cross
         // terms (a mirrored position carries a zero metric or folds onto a)
         const long long ci = (long long)a * g.nt + b;
-        const bool lo = b > 0, hi = b < g.nt - 1;
+        const bool lo = b > 0 && !zero, hi = b < g.nt - 1;
+        const bool up = hi && !zero;
         const T gtl = G[4 * gk + ci], gth = hi ? G[4 * gk + ci + 1] : T(0);
         const T qrl = T(0.25) * G[gk + ci];
         const T qrh = a < g.nr - 1 ? T(0.25) * G[gk + ci + g.nt] : T(0);
@@ -290,13 +321,13 @@ __device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>*
         const T cl0 = -gtl + qrh - qrl, clp = qrh + qtl, clm = -qrl - qtl;
         const long long base = (long long)a * g.rowlen + (long long)b * nh;
         const long long dp = a < g.nr - 1 ? g.rowlen : 0, dm = a > 0 ? g.rowlen : 0;
-        for (int j = tr; j < nh; j += pl.tpr) {
+        for (int j = tr; j < nh; j += tpr) {
             Vec2<T> z;
             z.x = ld_once(bv + base + j);
             z.y = ld_once(bv + g.P + base + j);
 #pragma unroll
             for (int side = 0; side < 2; ++side) {
-                const bool on = side ? hi : lo;
+                const bool on = side ? up : lo;
                 if (!on) continue;
                 const long long r0 = base + (side ? nh : -nh) + j;
                 const T c0 = side ? ch0 : cl0, cp = side ? chp : clp, cm = side ? chm : clm;
@@ -305,18 +336,18 @@ __device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>*
             }
             A[j] = z;
         }
-    } else if (live) {
+    } else {
         const long long ci = (long long)a * g.nt + b;
         const T gtl = G[4 * gk + ci];
         const T gth = b < g.nt - 1 ? G[4 * gk + ci + 1] : T(0);
         const long long base = (long long)a * g.rowlen + (long long)b * nh;
-        const bool lo = b > 0, hi = b < g.nt - 1;
-        for (int j0 = tr; j0 < nh; j0 += kLdBatch * pl.tpr) {
+        const bool lo = b > 0 && !zero, hi = b < g.nt - 1 && !zero;
+        for (int j0 = tr; j0 < nh; j0 += kLdBatch * tpr) {
             // the loads of a batch are all issued before any is used
             T e[kLdBatch], o[kLdBatch], el[kLdBatch], ol[kLdBatch], eh[kLdBatch], oh[kLdBatch];
 #pragma unroll
             for (int u = 0; u < kLdBatch; ++u) {
-                const int j = j0 + u * pl.tpr;
+                const int j = j0 + u * tpr;
                 if (j < nh) {
                     e[u] = ld_once(bv + base + j);
                     o[u] = ld_once(bv + g.P + base + j);
@@ -328,7 +359,7 @@ __device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>*
             }
 #pragma unroll
             for (int u = 0; u < kLdBatch; ++u) {
-                const int j = j0 + u * pl.tpr;
+                const int j = j0 + u * tpr;
                 if (j < nh) {
                     Vec2<T> z;
                     z.x = e[u];
@@ -346,6 +377,30 @@ __device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>*
             }
         }
     }
+}
+
+// Bodies take the logical block index (the batched form maps its blocks to
+// problems); buf and twS are the block's LDS.
+template <typename T, int NMAX, bool CROSS = false>
+__device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>* twS, Geo g,
+                                            const T* __restrict__ G, long long gk,
+                                            const T* __restrict__ bv, const T* __restrict__ x,
+                                            int parity, const Vec2<T>* __restrict__ tw,
+                                            const Vec2<T>* __restrict__ twN,
+                                            Vec2<T>* __restrict__ S, int rb, bool zero)
+{
+    const PlaneLaunch pl = plane_launch(g, parity, rb);
+    const int nh = g.nh;
+    for (int q = (int)threadIdx.x; q < nh / 2; q += pl.threads) twS[q] = tw[q];
+    const int rl = (int)threadIdx.x / pl.tpr, tr = (int)threadIdx.x - rl * pl.tpr;
+    const int ring = (int)blk * pl.rb + rl;
+    // threads past the block's rings (a batched launch of a fixed block
+    // size) only take part in the barrier
+    const bool live = rl < pl.rb && ring < pl.rings;
+    const int a = live ? ring / pl.rows : 0, bi = live ? ring - a * pl.rows : 0;
+    const int b = 2 * bi + parity;
+    Vec2<T>* A = buf + rl * nh;
+    if (live) plane_rhs<T, CROSS>(g, G, gk, bv, x, a, b, tr, pl.tpr, zero, A);
     __syncthreads(); // twiddles of the block (the ring's values are wave-local)
     if (!live) return;
     wave_fft<T, NMAX>(A, nh, tr, pl.tpr, twS, false);
@@ -362,20 +417,7 @@ __device__ __forceinline__ void d_plane_fwd(unsigned blk, Vec2<T>* buf, Vec2<T>*
         for (int u = 0; u < kLdBatch; ++u) {
             const int m = m0 + u * pl.tpr;
             if (m < nh) {
-                const Vec2<T> zm = Z[m];
-                const Vec2<T> zc = conjv(Z[m == 0 ? 0 : nh - m]);
-                // even part E = (zm + zc) / 2, odd part O = (zm - zc) / (2i)
-                Vec2<T> E, O;
-                E.x = T(0.5) * (zm.x + zc.x);
-                E.y = T(0.5) * (zm.y + zc.y);
-                O.x = T(0.5) * (zm.y - zc.y);
-                O.y = -T(0.5) * (zm.x - zc.x);
-                Vec2<T> X = E + cmul(w[u], O);
-                if (m == 0) { // modes 0 and nh: E + O and E - O, both real
-                    X.x = zm.x + zm.y;
-                    X.y = zm.x - zm.y;
-                }
-                out[m] = X;
+                out[m] = ring_mode<T>(m, Z[m], Z[m == 0 ? 0 : nh - m], w[u]);
             }
         }
     }
@@ -387,10 +429,11 @@ __global__ void __launch_bounds__(kBlock) k_plane_fwd(Geo g, const T* __restrict
                                                       const T* __restrict__ x, int parity,
                                                       const Vec2<T>* __restrict__ tw,
                                                       const Vec2<T>* __restrict__ twN,
-                                                      Vec2<T>* __restrict__ S, int rb)
+                                                      Vec2<T>* __restrict__ S, int rb, int zero)
 {
     __shared__ Vec2<T> buf[kPlaneLds], twS[kPlaneLds / 2];
-    d_plane_fwd<T, NMAX, CROSS>(blockIdx.x, buf, twS, g, G, gk, bv, x, parity, tw, twN, S, rb);
+    d_plane_fwd<T, NMAX, CROSS>(blockIdx.x, buf, twS, g, G, gk, bv, x, parity, tw, twN, S, rb,
+                                zero != 0);
 }
 
 // Inverse pivots of the Thomas elimination of every (row, mode) r-line of
@@ -488,10 +531,12 @@ struct TriLds {
 
 // UNI: nh >= 32, so a wavefront's lines are of one row (its off-diagonals
 // become scalar loads).
-template <typename T, bool UNI>
+// INLDS: S is the plane of theta row ldsrow alone, [a][2 nh], in LDS.
+template <typename T, bool UNI, bool INLDS = false>
 __device__ __forceinline__ void d_tri_chunk(unsigned blk, const TriLaunch& tl, const Geo& g,
                                             int parity, const TriTab<T>& tab,
-                                            T* __restrict__ S, TriLds<T>& sh)
+                                            T* __restrict__ S, TriLds<T>& sh,
+                                            unsigned ldsrow = 0)
 {
     constexpr int K = kTriChunk;
     const int rows = (g.nt - parity + 1) / 2, nh = g.nh, nr = g.nr;
@@ -501,7 +546,8 @@ __device__ __forceinline__ void d_tri_chunk(unsigned blk, const TriLaunch& tl, c
     const unsigned u = (blk * (unsigned)tl.gpb + (unsigned)grp) * 64u + (unsigned)lane;
     const bool live = grp < tl.gpb && u < (unsigned)tl.lanes;
     const unsigned t = live ? u >> 1 : 0u; // line
-    const unsigned bl = t / (unsigned)nh, m = t - bl * (unsigned)nh;
+    const unsigned bl = INLDS ? ldsrow : t / (unsigned)nh;
+    const unsigned m = INLDS ? t : t - bl * (unsigned)nh;
     const unsigned bi = UNI ? (unsigned)__builtin_amdgcn_readfirstlane((int)bl) : bl;
     // slot 0's imaginary lane carries mode nh
     const unsigned mp = m == 0 && (u & 1) ? (unsigned)nh : m;
@@ -516,7 +562,8 @@ __device__ __forceinline__ void d_tri_chunk(unsigned blk, const TriLaunch& tl, c
         d[k] = T(0);
         e[k] = T(0);
         if (a0 + k < nr && live) {
-            d[k] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(S) + (so + k * ss));
+            if constexpr (INLDS) d[k] = S[(a0 + k) * 2 * nh + (int)u];
+            else d[k] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(S) + (so + k * ss));
             e[k] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(tab.P) +
                                                (po + k * sp));
         }
@@ -574,8 +621,10 @@ __device__ __forceinline__ void d_tri_chunk(unsigned blk, const TriLaunch& tl, c
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
         above = fma_t(e[k], above, d[k]);
-        if (a0 + k < nr && live)
-            *reinterpret_cast<T*>(reinterpret_cast<char*>(S) + (so + k * ss)) = above;
+        if (a0 + k < nr && live) {
+            if constexpr (INLDS) S[(a0 + k) * 2 * nh + (int)u] = above;
+            else *reinterpret_cast<T*>(reinterpret_cast<char*>(S) + (so + k * ss)) = above;
+        }
     }
 }
 
@@ -686,29 +735,15 @@ __device__ __forceinline__ void d_plane_inv(unsigned blk, Vec2<T>* buf, Vec2<T>*
                 const int m = m0 + u * pl.tpr;
                 if (m < nh) {
                     xm[u] = X[m];
-                    xc[u] = conjv(X[m == 0 ? 0 : nh - m]);
-                    w[u] = conjv(twN[m]);
+                    xc[u] = X[m == 0 ? 0 : nh - m];
+                    w[u] = twN[m];
                 }
             }
 #pragma unroll
             for (int u = 0; u < kLdBatch; ++u) {
                 const int m = m0 + u * pl.tpr;
                 if (m < nh) {
-                    // E = (xm + xc) / 2, O = (xm - xc) conj(twN[m]) / 2, Z = E + i O
-                    Vec2<T> E, D;
-                    E.x = T(0.5) * (xm[u].x + xc[u].x);
-                    E.y = T(0.5) * (xm[u].y + xc[u].y);
-                    D.x = T(0.5) * (xm[u].x - xc[u].x);
-                    D.y = T(0.5) * (xm[u].y - xc[u].y);
-                    const Vec2<T> O = cmul(w[u], D);
-                    Vec2<T> z;
-                    z.x = E.x - O.y;
-                    z.y = E.y + O.x;
-                    if (m == 0) { // slot 0: modes 0 and nh
-                        z.x = T(0.5) * (xm[u].x + xm[u].y);
-                        z.y = T(0.5) * (xm[u].x - xm[u].y);
-                    }
-                    A[m] = z;
+                    A[m] = ring_value<T>(m, xm[u], xc[u], w[u]);
                 }
             }
         }
@@ -737,6 +772,123 @@ __global__ void __launch_bounds__(kBlock) k_plane_inv(Geo g, int parity,
 {
     __shared__ Vec2<T> buf[kPlaneLds], twS[kPlaneLds / 2];
     d_plane_inv<T, NMAX>(blockIdx.x, buf, twS, g, parity, tw, twN, S, x, rb);
+}
+
+// ---------------------------------------------------------------------------
+// A half-sweep in one launch, where a row's (r, phi) plane is small: a block
+// per relaxed theta row makes its right-hand side, transforms the rings,
+// solves the r-lines and transforms back without leaving LDS; the arithmetic
+// is that of the three kernels.  Bound by latency: three launches take 4 to
+// 6 us each whatever a small level holds, one takes the sum of their chains.
+// Measured, a half-sweep (n_r x n_phi/2 a row, three launches -> one): FP32
+// 16 x 16 12.0 -> 9.1 us, 32 x 32 13.0 -> 10.9, but 64 x 64 15.5 -> 24 and
+// 128 x 128 33 -> 75; FP64 12 x 16 17.0 -> 8.4, 24 x 32 13.2 -> 11.3, but
+// 48 x 64 15.8 -> 22: a larger plane gives one block per row too long a chain,
+// on few CUs.  The line lies at the largest square plane that gained.
+// ---------------------------------------------------------------------------
+
+constexpr int kRowCells = 1024; // complex values of the largest plane
+
+__host__ __device__ inline bool plane_row_fits(const Geo& g)
+{
+    return tri_chunked(g) && g.nh <= kSmallRing && (long long)g.nr * g.nh <= kRowCells;
+}
+
+// threads of a row's block: a ring's lanes for every r (or all that fit), and
+// the wavefronts of an r-line
+__host__ __device__ inline int plane_row_threads(const Geo& g)
+{
+    const int tpr = g.nh / 2 < 64 ? g.nh / 2 : 64;
+    const int nw = (g.nr + kTriChunk - 1) / kTriChunk, groups = (2 * g.nh + 63) / 64;
+    int t = (g.nr * tpr + 63) / 64;
+    if (t < nw * groups) t = nw * groups;
+    return 64 * (t < kTriWaves ? t : kTriWaves);
+}
+
+template <typename T>
+struct PlaneRowLds {
+    Vec2<T> A[kRowCells], tw[kSmallRing / 2], twN[kSmallRing];
+    TriLds<T> tri;
+};
+
+template <typename T, bool CROSS>
+__device__ __forceinline__ void d_plane_row(unsigned bi, PlaneRowLds<T>& sh, const Geo& g,
+                                            const T* __restrict__ G, long long gk,
+                                            const T* __restrict__ bv, T* __restrict__ x, int parity,
+                                            const Vec2<T>* __restrict__ tw,
+                                            const Vec2<T>* __restrict__ twN,
+                                            const T* __restrict__ piv, bool zero)
+{
+    constexpr int V = kSmallRing / 64; // values of a ring per lane, at most
+    const int nh = g.nh, nr = g.nr, b = 2 * (int)bi + parity;
+    const int tpr = nh / 2 < 64 ? nh / 2 : 64, threads = (int)blockDim.x;
+    for (int q = (int)threadIdx.x; q < nh; q += threads) {
+        if (q < nh / 2) sh.tw[q] = tw[q];
+        sh.twN[q] = twN[q];
+    }
+    // the lanes of a ring are of one wavefront: rings go by wavefronts' worths
+    const int rl = (int)threadIdx.x / tpr, tr = (int)threadIdx.x - rl * tpr, rings = threads / tpr;
+    for (int a = rl; a < nr; a += rings)
+        plane_rhs<T, CROSS>(g, G, gk, bv, x, a, b, tr, tpr, zero, sh.A + a * nh);
+    __syncthreads(); // twiddles
+    for (int a = rl; a < nr; a += rings) {
+        Vec2<T>* A = sh.A + a * nh;
+        wave_sync();
+        wave_fft<T, kSmallRing>(A, nh, tr, tpr, sh.tw, false);
+        Vec2<T> X[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const int m = tr + i * tpr;
+            if (m < nh) X[i] = ring_mode<T>(m, A[m], A[m == 0 ? 0 : nh - m], sh.twN[m]);
+        }
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+            if (tr + i * tpr < nh) A[tr + i * tpr] = X[i];
+    }
+    __syncthreads();
+    // the r-lines, as many groups of 64 at a time as the block has wavefronts for
+    TriLaunch tl;
+    tl.lanes = 2 * nh;
+    tl.nw = (nr + kTriChunk - 1) / kTriChunk;
+    tl.gpb = (threads >> 6) / tl.nw;
+    const TriTab<T> tab = tri_tab<T>(g, parity, const_cast<T*>(piv));
+    for (unsigned k = 0; k * 64u * (unsigned)tl.gpb < (unsigned)tl.lanes; ++k) {
+        d_tri_chunk<T, true, true>(k, tl, g, parity, tab, reinterpret_cast<T*>(sh.A), sh.tri, bi);
+        __syncthreads();
+    }
+    const T s = T(1) / T(nh);
+    for (int a = rl; a < nr; a += rings) {
+        Vec2<T>* A = sh.A + a * nh;
+        Vec2<T> Z[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const int m = tr + i * tpr;
+            if (m < nh) Z[i] = ring_value<T>(m, A[m], A[m == 0 ? 0 : nh - m], sh.twN[m]);
+        }
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+            if (tr + i * tpr < nh) A[tr + i * tpr] = Z[i];
+        wave_sync();
+        wave_fft<T, kSmallRing>(A, nh, tr, tpr, sh.tw, true);
+        const long long base = (long long)a * g.rowlen + (long long)b * nh;
+        for (int j = tr; j < nh; j += tpr) {
+            const Vec2<T> v = A[j];
+            x[base + j] = v.x * s;
+            x[g.P + base + j] = v.y * s;
+        }
+    }
+}
+
+template <typename T, bool CROSS>
+__global__ void __launch_bounds__(64 * kTriWaves)
+    k_plane_row(Geo g, const T* __restrict__ G, long long gk, const T* __restrict__ bv,
+                T* __restrict__ x, int parity, const Vec2<T>* __restrict__ tw,
+                const Vec2<T>* __restrict__ twN, const T* __restrict__ piv, int zero)
+{
+    __shared__ PlaneRowLds<T> sh;
+    d_plane_row<T, CROSS>(blockIdx.x, sh, g, G, gk, bv, x, parity, tw, twN, piv, zero != 0);
 }
 
 } // namespace cps

@@ -229,3 +229,46 @@ def test_elimination_chunks_and_remainders(shape, map_):
             x = want
     finally:
         s.close()
+
+
+# A half-sweep in one launch: (r, phi) planes of up to 1024 complex values on
+# rings of up to 256, here at that size by n_r and by ring and one step above
+# it (three launches, rings within and past a wavefront's lines), the shortest
+# ring, and a last group of rings that is not full.
+ROWS = [(32, 4, 64), (34, 4, 64), (64, 6, 32), (66, 4, 32), (4, 6, 512), (6, 4, 512), (256, 4, 4),
+        (18, 6, 16)]
+
+
+@pytest.mark.parametrize("map_", [MAP_IDENTITY, MAP_OBLATE], ids=["box", "oblate"])
+@pytest.mark.parametrize("shape", ROWS, ids=lambda s: "x".join(map(str, s)))
+def test_half_sweep_launch_forms(shape, map_):
+    """Bounds and geometry as test_elimination_chunks_and_remainders."""
+    test_elimination_chunks_and_remainders(shape, map_)
+
+
+@pytest.mark.parametrize("shape", [(64, 8, 64), (128, 8, 128)], ids=["one-launch", "three-launch"])
+@pytest.mark.parametrize("map_", [MAP_IDENTITY, MAP_OBLATE], ids=["box", "oblate"])
+def test_vcycle_starts_coarse_levels_from_zero(shape, map_):
+    """The first half-sweep of a coarse level takes its iterate as zero and
+    does not read it, in either launch form: the second of two V-cycles, whose
+    coarse arrays hold the first's values, against the oracle's to 1e-11
+    relative (three levels of the half-sweeps' 1e-12)."""
+    f = 0.1 if map_ == MAP_OBLATE else 0.0
+    g = Shell(*shape, map=map_, flattening=f, r_inner=1.5, r_outer=1.5 + 0.25 * shape[0])
+    s = cps.Solver(g, precision=0, accel=0, smoother=1, n_levels=3)
+    try:
+        mg = O.Multigrid(g, n_levels=3)
+        pm = plane.PlaneMultigrid(mg, nu=2)
+        rng = np.random.default_rng(6)
+        x = rng.standard_normal(shape) * 0.1
+        for _ in range(2):
+            b = rng.standard_normal(shape)
+            b -= b.mean()
+            want = pm.vcycle(b, x)
+            xd = dev(x).flatten()
+            cps.cps_debug_vcycle(s.h, dev(b).flatten(), xd)
+            x = host(xd).reshape(shape)
+            log("zero start", map_, shape, relmax(x, want))
+            assert relmax(x, want) < 1e-11, relmax(x, want)
+    finally:
+        s.close()
