@@ -1956,6 +1956,27 @@ double* line_scratch_ptr()
     return g_scratch_dev[dev];
 }
 
+// the eliminated open lines along dir (k_line_factor's tables)
+void line_open(cps_handle* h, int dir, const double* Fm, const double* Fi, const double* Fh,
+               const double* Fx, const double* rhs, double* psi)
+{
+    const LevelMem& m = h->lv[0];
+    const int lines = dir == 0 ? m.nt : m.nr, n = dir == 0 ? m.nr : m.nt;
+    if (line_chunked(n)) {
+        const LineLaunch l = line_launch(m.nr, m.nt, m.np, dir);
+        const bool uni = m.np % 64 == 0;
+        auto k = dir == 0 ? (uni ? k_line_chunk<0, true> : k_line_chunk<0, false>)
+                          : (uni ? k_line_chunk<1, true> : k_line_chunk<1, false>);
+        k<<<(unsigned)l.blocks, 64 * l.nw * l.gpb, 0, h->stream>>>(m.nr, m.nt, m.np, Fm, Fi, Fh, Fx,
+                                                                   rhs, psi);
+    } else {
+        const long long threads = (long long)lines * m.np;
+        auto k = dir == 0 ? k_line_open<0> : k_line_open<1>;
+        k<<<nblk(threads), kBlock, 0, h->stream>>>(m.nr, m.nt, m.np, Fm, Fi, Fh, Fx, rhs, psi);
+    }
+    LAUNCH_CHECK();
+}
+
 // cps_line_solve with its tables formed in line_scratch on every call:
 // the same kernels in the same order, launches only.
 void line_solve_noalloc(cps_handle* h, int dir, double coef, const LineBC& bc,
@@ -1997,14 +2018,7 @@ void line_solve_noalloc(cps_handle* h, int dir, double coef, const LineBC& bc,
         k_line_factor<<<nblk(lines), kBlock, 0, h->stream>>>(m.nr, m.nt, dir, coef, bc, R, Jf, Jc,
                                                              Fm, Fi, Fh, Fx);
         LAUNCH_CHECK();
-        const long long threads = (long long)lines * m.np;
-        if (dir == 0)
-            k_line_open<0><<<nblk(threads), kBlock, 0, h->stream>>>(m.nr, m.nt, m.np, Fm, Fi, Fh,
-                                                                    Fx, rhs, psi);
-        else
-            k_line_open<1><<<nblk(threads), kBlock, 0, h->stream>>>(m.nr, m.nt, m.np, Fm, Fi, Fh,
-                                                                    Fx, rhs, psi);
-        LAUNCH_CHECK();
+        line_open(h, dir, Fm, Fi, Fh, Fx, rhs, psi);
         return;
     }
     double* tw = T;
@@ -2055,14 +2069,7 @@ void line_solve(cps_handle* h, int dir, double coef, const LineBC& bc, const dou
             h->lf_bc[dir] = bc;
         }
         views();
-        const long long threads = (long long)lines * m.np;
-        if (dir == 0)
-            k_line_open<0><<<nblk(threads), kBlock, 0, h->stream>>>(m.nr, m.nt, m.np, Fm, Fi, Fh,
-                                                                    Fx, rhs, psi);
-        else
-            k_line_open<1><<<nblk(threads), kBlock, 0, h->stream>>>(m.nr, m.nt, m.np, Fm, Fi, Fh,
-                                                                    Fx, rhs, psi);
-        LAUNCH_CHECK();
+        line_open(h, dir, Fm, Fi, Fh, Fx, rhs, psi);
         return;
     }
     if (fft_lines(h, rhs, psi)) {

@@ -14,10 +14,12 @@
 //  - r- and theta-lines: the Thomas algorithm (eq. (FIBRE_TA1)-(FIBRE_TA2)).
 //    On a phi-invariant map a line's coefficients depend on one index (b for
 //    r-lines, a for theta-lines), so k_line_factor runs the elimination of
-//    the coefficients once per distinct line; k_line_open then streams the
-//    right-hand side down and up every line, one thread per line, lines
-//    consecutive in phi across a wavefront, a batch of steps of loads in
-//    flight.  psi holds the eliminated right-hand side between the sweeps.
+//    the coefficients once per distinct line.  Lines of up to 256 cells:
+//    k_line_chunk, 16 cells of a line per thread.  Longer ones: k_line_open
+//    streams the right-hand side down and up every line, one thread per line,
+//    a batch of steps of loads in flight; psi holds the eliminated right-hand
+//    side between the sweeps.  Both: lines consecutive in phi across a
+//    wavefront.
 //  - phi-lines: the paper's periodic form (eq. (FIBRE_TAP1)-(FIBRE_TAP8)):
 //    the first n - 1 unknowns solve the open system for g and for the corner
 //    column, the last follows from the closing row, and psi = psi1 +
@@ -130,7 +132,136 @@ __global__ void __launch_bounds__(kBlock) k_ring_tables(int np, double* __restri
     }
 }
 
-// Open lines along d (0 r, 1 theta): one thread per (other index, c).
+// Open lines along d (0 r, 1 theta) of at most kLineChunk * kLineWaves cells:
+// a line is split over the wavefronts of a block, kLineChunk cells of it in
+// each thread's registers, so that the right-hand side is read and psi written
+// once (the streaming form below also writes and reads the eliminated values)
+// and a short line's cells are all in flight at once.  Both recurrences are
+// affine: each chunk forms its map of the value entering it, the chunks'
+// maps are composed through LDS, and the cells then follow from the true
+// entering value.  Bound by HBM at large sizes and by the latency of one
+// read, two exchanges and one write at small ones.
+// Measured (streaming -> chunks): 192 x 256 x 512, r 146 -> 80 us (5.0 TB/s
+// read and written), theta 174 -> 93 us (4.3); 32 x 32 x 64, 13.5 -> 6.2 us
+// each.  Past 256 cells a line no longer fits a block's 16 wavefronts.
+constexpr int kLineChunk = 16, kLineWaves = 16;
+
+struct LineLaunch {
+    int nw, gpb; // wavefronts of a line, groups of 64 lines a block
+    long long blocks;
+};
+
+__host__ __device__ inline bool line_chunked(int n) { return n <= kLineChunk * kLineWaves; }
+
+__host__ __device__ inline LineLaunch line_launch(int nr, int nt, int np, int d)
+{
+    LineLaunch l;
+    const int n = d == 0 ? nr : nt;
+    const long long groups = ((long long)(d == 0 ? nt : nr) * np + 63) / 64;
+    l.nw = (n + kLineChunk - 1) / kLineChunk;
+    // blocks of at least 4 wavefronts once there are enough for every CU
+    l.gpb = l.nw >= 4 || groups <= 1024 ? 1 : 4 / l.nw;
+    l.blocks = (groups + l.gpb - 1) / l.gpb;
+    return l;
+}
+
+// UNI: n_phi a multiple of 64, so a wavefront's lines share their coefficients
+// (scalar loads).
+template <int D, bool UNI>
+__global__ void __launch_bounds__(64 * kLineWaves)
+    k_line_chunk(int nr, int nt, int np, const double* __restrict__ Fm,
+                 const double* __restrict__ Fi, const double* __restrict__ Fh,
+                 const double* __restrict__ Fx, const double* rhs, double* psi)
+{
+    constexpr int K = kLineChunk;
+    __shared__ Vec2<double> sf[kLineWaves][64], sb[kLineWaves][64];
+    const int other = D == 0 ? nt : nr, n = D == 0 ? nr : nt;
+    const int nw = (n + K - 1) / K, gpb = (int)(blockDim.x >> 6) / nw;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & 63;
+    const int grp = wv / nw, w = wv - grp * nw; // the line's chunk w
+    const long long u = ((long long)blockIdx.x * gpb + grp) * 64 + lane;
+    const bool live = u < (long long)other * np;
+    const unsigned t = live ? (unsigned)u : 0u;
+    const unsigned pl = t / (unsigned)np, c = t - pl * (unsigned)np;
+    const int p = UNI ? __builtin_amdgcn_readfirstlane((int)pl) : (int)pl;
+    const int i0 = w * K;
+    const long long stride = D == 0 ? (long long)nt * np : np;
+    const long long base = (D == 0 ? (long long)p * np : (long long)p * nt * np) + c + i0 * stride;
+    const double* fm = Fm + (long long)p * n + i0;
+    const double* fi = Fi + (long long)p * n + i0;
+    const double* fh = Fh + (long long)p * n + i0;
+    double d[K], f[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        d[k] = 0.0;
+        if (i0 + k < n && live) d[k] = rhs[base + k * stride];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) f[k] = i0 + k < n ? -fm[k] : 0.0;
+    const double ex0 = w == 0 ? Fx[2 * p] : 0.0, exl = n > 1 ? Fx[2 * p + 1] : 0.0;
+    d[0] += ex0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) d[k] += i0 + k == n - 1 ? exl : 0.0;
+    // down: g_i = v_i - m_i g_{i-1}
+    double below = 0.0;
+    if (nw > 1) {
+        Vec2<double> v;
+        v.x = 0.0;
+        v.y = 1.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            v.x = __builtin_fma(f[k], v.x, d[k]);
+            v.y *= f[k];
+        }
+        sf[wv][lane] = v;
+        __syncthreads();
+        for (int q = 0; q < w; ++q) {
+            const Vec2<double> m = sf[wv - w + q][lane];
+            below = __builtin_fma(m.y, below, m.x);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (i0 + k < n) {
+            below = __builtin_fma(f[k], below, d[k]);
+            d[k] = below;
+        }
+    // up: x_i = (g_i - c_i x_{i+1}) / b'_i
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (i0 + k < n) {
+            const double iv = fi[k];
+            f[k] = -fh[k] * iv;
+            d[k] *= iv;
+        }
+    double above = 0.0;
+    if (nw > 1) {
+        Vec2<double> v;
+        v.x = 0.0;
+        v.y = 1.0;
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k)
+            if (i0 + k < n) {
+                v.x = __builtin_fma(f[k], v.x, d[k]);
+                v.y *= f[k];
+            }
+        sb[wv][lane] = v;
+        __syncthreads();
+        for (int q = nw - 1; q > w; --q) {
+            const Vec2<double> m = sb[wv - w + q][lane];
+            above = __builtin_fma(m.y, above, m.x);
+        }
+    }
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k)
+        if (i0 + k < n) {
+            above = __builtin_fma(f[k], above, d[k]);
+            if (live) psi[base + k * stride] = above;
+        }
+}
+
+// Longer open lines along d (0 r, 1 theta): one thread per (other index, c).
 template <int D>
 __global__ void __launch_bounds__(kBlock) k_line_open(int nr, int nt, int np,
                                                       const double* __restrict__ Fm,

@@ -163,3 +163,35 @@ def test_degenerate_cases():
         s.close()
     want = O.divergence(g2, u)
     assert np.abs(got - want).max() <= 1e-13 * np.abs(want).max()
+
+
+# The open lines' forms by their length n: one chunk of 16 cells that is full,
+# one cell pair into a second and a third, the most a block holds (256) and
+# the streaming form past it; rings of whole wavefronts (n_phi % 64 == 0,
+# shared coefficients) and others; and, with n = 16, blocks of four groups of
+# 64 lines whose last one is half empty (136 x 496 lines).
+OPEN = [(0, (16, 4, 64)), (1, (4, 18, 64)), (0, (34, 6, 20)), (1, (6, 34, 128)), (0, (256, 8, 64)),
+        (1, (4, 256, 12)), (0, (258, 4, 12)), (1, (4, 258, 20)), (0, (16, 136, 496))]
+
+
+@pytest.mark.parametrize("bc", BCS[:2], ids=["noflux", "values"])
+@pytest.mark.parametrize("d,shape", OPEN, ids=lambda v: v if isinstance(v, int) else "x".join(map(str, v)))
+def test_open_line_forms(d, shape, bc):
+    """Per entry to 1e-11 of the largest, out of place and in place: coef falls
+    with the line's length squared, so that a line's condition number stays
+    below 4 * 1.7 * 64 * 4 ~ 2e3, and 16 eps cond = 7e-12."""
+    g = Shell(*shape, radial_stretch=1.0)
+    coef = 1.7 * (8.0 / shape[d]) ** 2
+    rhs = np.random.default_rng(50 + d).standard_normal(shape)
+    want = O.line_solve(g, d, coef, rhs, bc)
+    s = cps.Solver(g, precision=0, n_levels=1 if g.cells <= 4096 else 0)
+    try:
+        x = dev(rhs).flatten()
+        got = host(s.line_solve(d, coef, x, bc)).reshape(shape)
+        s.line_solve(d, coef, x, bc, out=x)
+        err = np.abs(got - want).max() / np.abs(want).max()
+        log("open lines", d, shape, err)
+        assert err <= 1e-11, err
+        assert np.array_equal(got.ravel(), host(x))
+    finally:
+        s.close()
