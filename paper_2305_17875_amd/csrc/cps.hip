@@ -720,13 +720,16 @@ void vpre_tile(cps_handle* h, int l, const T* b, T* x, T* bc)
     LAUNCH_CHECK();
 }
 
+// dot: partial sums of b . xo in h->partial; returns their number
 template <typename T>
-void vpost_tile(cps_handle* h, int l, const T* b, const T* xi, T* xo, const T* e)
+long long vpost_tile(cps_handle* h, int l, const T* b, const T* xi, T* xo, const T* e, bool dot)
 {
     const Level<T> L = view<T>(h, l);
     k_vpost_tile<T><<<tile_count(L.g), kTileThreads, 0, h->stream>>>(L.g, L.G, L.gk, b, xi, xo,
-                                                                      h->lv[l + 1].geo, e);
+                                                                      h->lv[l + 1].geo, e,
+                                                                      dot ? h->partial.p : nullptr);
     LAUNCH_CHECK();
+    return dot ? tile_count(L.g) : 0;
 }
 
 // The same of a large level (march.hpp): pre writes the red cells of its
@@ -804,12 +807,12 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
         const T* b = l == 0 ? b0 : bl<T>(h, l);
         T* x = l == 0 ? x0 : xl<T>(h, l);
         const T* e = l + 1 == L - 1 ? xl<T>(h, l + 1) : xfin<T>(h, l + 1);
-        if (l == 0 && tile0) { // prolongation and smoothing, xt -> x0 (no dot sums)
-            vpost_tile<T>(h, 0, b, xtl<T>(h, 0), x, e);
+        if (l == 0 && tile0) { // prolongation and smoothing, xt -> x0
+            parts = vpost_tile<T>(h, 0, b, xtl<T>(h, 0), x, e, dot);
             continue;
         }
         if (l > 0 && h->lv[l].tile) { // prolongation and smoothing, into xt
-            vpost_tile<T>(h, l, b, x, xtl<T>(h, l), e);
+            vpost_tile<T>(h, l, b, x, xtl<T>(h, l), e, false);
             continue;
         }
         if (l == 0 && march0) {
@@ -1361,7 +1364,7 @@ void build(cps_handle* h)
     }
     const long long n0 = h->lv[0].n;
     // two passes' (or two reductions') partial sums side by side
-    h->partial.alloc(2 * std::max<long long>(nblk(n0), kMaxGrid) + 64);
+    h->partial.alloc(2 * std::max<long long>({nblk(n0), kMaxGrid, tile_count(h->lv[0].geo)}) + 64);
     h->sc.alloc(S_COUNT);
     {
         MemLock lk(g_capture_mu);
@@ -1389,7 +1392,7 @@ void build(cps_handle* h)
     for (int l = 0; l + 1 < h->L; ++l) {
         LevelMem& m = h->lv[l];
         const bool point7 = marching(h) && h->ncol == 2 && h->opts.smoother == 0;
-        m.tile = point7 && tile_fits(m.geo, mixed);
+        m.tile = point7 && tile_fits(m.geo, l, mixed);
         m.march = point7 && !m.tile && march_fits(m.geo);
         if (m.march) {
             m.mg = march_grid(m.geo, mixed);

@@ -102,7 +102,8 @@ size_t estimate_bytes(const cps_grid& g, const cps_opts& o)
         if (mixed) s += 9 * gk * 4 + n * 4 * (l + 1 < L ? 3 : 2);
         else s += n * 8 * ((l > 0 ? 2 : 0) + (l + 1 < L ? 1 : 0));
         // the tile path's second iterate (small levels, point smoother)
-        if (l + 1 < L && n <= (size_t)tile_max_cells(mixed)) s += n * (mixed ? 4 : 8);
+        if (l + 1 < L && tile_fits(make_geo(dims[l][0], dims[l][1], dims[l][2]), l, mixed))
+            s += n * (mixed ? 4 : 8);
         // the marching path's metrics table (large levels)
         if (l + 1 < L && n > (size_t)kMarchCells)
             s += (size_t)march_table_words(make_geo(dims[l][0], dims[l][1], dims[l][2])) *

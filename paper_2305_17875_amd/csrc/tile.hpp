@@ -39,41 +39,37 @@ constexpr int kTileThreads = 1024;  // threads per tile block
 constexpr int kPreHalo = 5, kPostHalo = 4;
 constexpr int kPreR = kTile + 2 * kPreHalo;   // 18
 constexpr int kPostR = kTile + 2 * kPostHalo; // 16
-constexpr int kResR = kTile + 2;              // residual box: the tile +- 1
 constexpr int kCoarseR = kTile / 2 + 6;       // coarse correction box of post
 
 // A level takes the tile path when it is small enough that its launches
-// dominate and its rings split into whole tiles (the finest level only in
-// cycles from a zero iterate; its Krylov dot products then come from a
-// separate reduction).  A tile block
-// takes 8-12 us (its phases are LDS-latency bound); on the paper-scale
-// shell the 24 x 32 x 64 and 12 x 16 x 32 levels gain (pre + post 21 and
-// 17 us against 46 and 38 us of per-kernel launches), the 48 x 64 x 128
-// level does not (768 tiles at one 117 KB block per CU: 61 against 52 us).
-// FP32 tiles take half the LDS (58 KB pre, 43 KB post), two blocks share a
-// CU, and the 48 x 64 x 128 level runs in two rounds instead of three.
+// dominate (the finest level only in cycles from a zero iterate); its rings
+// need not be whole tiles.  FP32: up to 512 K cells (48 x 64 x 128 in two
+// rounds of blocks: 28 us against 52 of eleven per-kernel launches).  FP64:
+// up to 64 K cells (24 x 32 x 64: 15 us against 46), and coarse levels whose
+// rows are not whole wavefronts, which the per-kernel passes take a cell a
+// thread, up to 256 K (40 x 48 x 72: 21 us against 45; 20 x 24 x 36: 15
+// against 45).  The finest level keeps the per-kernel passes above 64 K: their
+// profiling classes time them one by one.
 constexpr long long kTileMaxCells = 1LL << 16;
+constexpr long long kTileMaxRagged = 1LL << 18;
 constexpr long long kTileMaxCells32 = 1LL << 19;
 
-__host__ __device__ inline long long tile_max_cells(bool fp32)
+// level l of the hierarchy
+__host__ __device__ inline bool tile_fits(const Geo& g, int l, bool fp32)
 {
-    return fp32 ? kTileMaxCells32 : kTileMaxCells;
-}
-
-__host__ __device__ inline bool tile_fits(const Geo& g, bool fp32 = false)
-{
-    return g.np % kTile == 0 && g.nr % 2 == 0 && g.nt % 2 == 0 &&
-           (long long)g.nr * g.nt * g.np <= tile_max_cells(fp32);
+    const long long most = fp32 ? kTileMaxCells32
+                                : (l > 0 && g.nh % 64 != 0 ? kTileMaxRagged : kTileMaxCells);
+    return g.nr % 2 == 0 && g.nt % 2 == 0 && (long long)g.nr * g.nt * g.np <= most;
 }
 
 __host__ __device__ inline int tile_count(const Geo& g)
 {
-    return cdiv(g.nr, kTile) * cdiv(g.nt, kTile) * (g.np / kTile);
+    return cdiv(g.nr, kTile) * cdiv(g.nt, kTile) * cdiv(g.np, kTile);
 }
 
 __device__ __forceinline__ void tile_origin(const Geo& g, int t, int& A0, int& B0, int& C0)
 {
-    const int nc = g.np / kTile, nb = cdiv(g.nt, kTile);
+    const int nc = cdiv(g.np, kTile), nb = cdiv(g.nt, kTile);
     C0 = (t % nc) * kTile;
     t /= nc;
     B0 = (t % nb) * kTile;
@@ -108,51 +104,119 @@ __device__ __forceinline__ void tile_metrics(const Geo& g, const T* __restrict__
     m[5] = T(1) / -(m[0] + m[1] + m[2] + m[3] + m[4] + m[4]);
 }
 
+// Both kernels: a thread owns NP phi pairs of one row (a, b) of the box (a pair
+// is one red and one black cell), pair t of the row's thread j being number u
+// with t = j + u STEP.  Indices are formed once; the row's metrics, the right-
+// hand sides and the thread's own values stay in registers, and a pass reads
+// from LDS only the five neighbours that other threads own.  x in LDS is
+// [colour][u][thread], so that every read and write of a wavefront is of
+// consecutive words: the r and theta neighbours of a pair's cell of one colour
+// are the other colour's cells of the pairs of the rows around, at a fixed
+// thread distance.
+// Bound by the chain of a launch: about 2 us to start, 2 to the first values,
+// 0.5 to 0.9 an LDS exchange, one write.  Measured against one cell per thread
+// and pass with indices, metrics and b in LDS, FP64 pre + post: 32 x 32 x 32
+// 10.4 + 8.6 -> 8.6 + 7.3 us, 24 x 32 x 64 9.7 + 7.3 -> 7.8 + 6.7; FP32
+// 48 x 64 x 128 17.1 + 13.7 -> 15.1 + 12.5.  48 KB of LDS and 62 registers let
+// two FP64 blocks share a CU (before: one, of 117 KB).
+
+// tile_metrics of a thread's row in registers; all zero past the walls
+template <typename T>
+struct TileRow {
+    T rl, rh, tl, th, p, inv;
+    bool in;
+};
+
+template <typename T>
+__device__ __forceinline__ TileRow<T> tile_row(const Geo& g, const T* __restrict__ G, long long gk,
+                                               int a, int b, bool in)
+{
+    TileRow<T> m;
+    m.in = in;
+    m.rl = m.rh = m.tl = m.th = m.p = m.inv = T(0);
+    if (in) {
+        T v[6];
+        tile_metrics(g, G, gk, a, b, v);
+        m.rl = v[0];
+        m.rh = v[1];
+        m.tl = v[2];
+        m.th = v[3];
+        m.p = v[4];
+        m.inv = v[5];
+    }
+    return m;
+}
+
+// phi index c of a box cell (no more than 13 past either end of the ring) on the ring
+__device__ __forceinline__ int wrap_near(int c, int np)
+{
+    if (np < 16) return wrapi(c, np);
+    return c < 0 ? c + np : (c >= np ? c - np : c);
+}
+
 template <typename T>
 struct TilePreLds {
-    T x[kPreR * kPreR * kPreR];
-    T b[kPreR * kPreR * kPreR]; // right-hand side; then the restriction's partial sums
-    T m[kPreR * kPreR][6];
-    T r[kResR * kResR * kResR];
+    T x[2][3][kTileThreads];
 };
 
 template <typename T>
 struct TilePostLds {
-    T x[kPostR * kPostR * kPostR];
-    T b[kPostR * kPostR * kPostR];
-    T m[kPostR * kPostR][6];
+    T x[2][2][kTileThreads];
     T e[kCoarseR * kCoarseR * kCoarseR];
 };
 
-// One colour pass over the region box [s, R - s)^3 (clipped to the domain in
-// r and theta) of a tile's LDS copy with origin (ra, rb, rc): each cell of
-// the colour takes x = (b - S) / D from its six neighbours.  zero: the
-// first pass from a zero iterate, x = b / D, reads no neighbour (so s may
-// be 0: the region's outer layer has none in LDS).  Cells past the walls
-// keep metrics 0 and are never updated.
-template <typename T, int R>
-__device__ __forceinline__ void tile_pass(const Geo& g, int ra, int rb, int rc, int s, int col,
-                                          bool zero, T* __restrict__ x, const T* __restrict__ bl,
-                                          const T (*__restrict__ m)[6])
-{
-    const int a_lo = max(s, -ra), a_hi = min(R - s, g.nr - ra);
-    const int b_lo = max(s, -rb), b_hi = min(R - s, g.nt - rb);
-    const int na = a_hi - a_lo, nb = b_hi - b_lo, nh = (R - 2 * s) / 2;
-    const int cells = na * nb * nh;
-    for (int i = (int)threadIdx.x; i < cells; i += (int)blockDim.x) {
-        const int t = i % nh, rowi = i / nh;
-        const int bb = b_lo + rowi % nb, aa = a_lo + rowi / nb;
-        const int cc = s + 2 * t + ((col + ra + aa + rb + bb + rc + s) & 1);
-        const int k = (aa * R + bb) * R + cc;
-        const T* mm = m[aa * R + bb];
-        if (zero) {
-            x[k] = bl[k] * mm[5];
-            continue;
-        }
-        const T S = mm[1] * x[k + R * R] + mm[0] * x[k - R * R] + mm[3] * x[k + R] +
-                    mm[2] * x[k - R] + mm[4] * (x[k - 1] + x[k + 1]);
-        x[k] = (bl[k] - S) * mm[5];
+// a thread's place in the box: its row, its pairs t = j + u STEP, and the
+// distance in LDS from a pair to the one whose cell is the phi neighbour of
+// the pair's red cell (the other phi neighbour is the pair's own black cell);
+// of its black cell the neighbour is on the other side
+template <int R, int NP>
+struct TilePos {
+    static constexpr int STEP = R / 2 / NP;
+    int aa, bb, j, red, dn[2];
+
+    __device__ __forceinline__ TilePos(int ra, int rb, int rc)
+    {
+        const int tid = (int)threadIdx.x, row = tid / STEP;
+        j = tid - row * STEP;
+        aa = row / R;
+        bb = row - aa * R;
+        // box parity (cc & 1) of the row's red cells
+        red = (ra + aa + rb + bb + rc) & 1;
+        const int up = j == STEP - 1 ? kTileThreads - (STEP - 1) : 1;
+        const int lo = j == 0 ? STEP - 1 - kTileThreads : -1;
+        dn[0] = red ? up : lo;
+        dn[1] = red ? lo : up;
     }
+    __device__ __forceinline__ bool rows(int s) const // row in [s, R - s)^2
+    {
+        return aa >= s && aa < R - s && bb >= s && bb < R - s;
+    }
+    __device__ __forceinline__ bool cell(int u, int col, int s) const // cell in [s, R - s)
+    {
+        const int cc = 2 * (j + u * STEP) + (red ^ col);
+        return cc >= s && cc < R - s;
+    }
+};
+
+// One pass of colour COL over the region [s, R - s)^3 of a tile's LDS copy:
+// each cell takes x = (b - S) / D from its six neighbours.
+template <int COL, int R, int NP, typename T>
+__device__ __forceinline__ void tile_pass(const TileRow<T>& m, const TilePos<R, NP>& p, int s,
+                                          T (&x)[2][NP], const T (&bw)[2][NP],
+                                          T (&X)[2][NP][kTileThreads])
+{
+    constexpr int STEP = TilePos<R, NP>::STEP;
+    if (!m.in || !p.rows(s)) return;
+    const int tid = (int)threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < NP; ++u)
+        if (p.cell(u, COL, s)) {
+            const T* n = &X[1 - COL][u][tid];
+            const T S = m.rh * n[R * STEP] + m.rl * n[-R * STEP] + m.th * n[STEP] +
+                        m.tl * n[-STEP] + m.p * (x[1 - COL][u] + n[p.dn[COL]]);
+            x[COL][u] = (bw[COL][u] - S) * m.inv;
+            X[COL][u][tid] = x[COL][u];
+        }
 }
 
 // Pre: bc (the tile's coarse cells) = R r, r = b - A x, x = 2 red-black
@@ -162,206 +226,183 @@ __device__ __forceinline__ void d_vpre_tile(Blk bk, Geo f, const T* __restrict__
                                             const T* __restrict__ bv, T* __restrict__ x,
                                             Geo c, T* __restrict__ bc, TilePreLds<T>& sh)
 {
-    constexpr int R = kPreR, H = kPreHalo;
+    constexpr int R = kPreR, H = kPreHalo, NP = 3, STEP = TilePos<R, NP>::STEP;
+    static_assert(R * R * STEP <= kTileThreads, "threads of a tile");
     if ((int)bk.L >= tile_count(f)) return; // whole block
     int A0, B0, C0;
     tile_origin(f, (int)bk.L, A0, B0, C0);
     const int ra = A0 - H, rb = B0 - H, rc = C0 - H;
-    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
-    // every load of a thread goes out before any is stored (a loop that
-    // stores each value before the next load waits on every one in turn)
-    constexpr int NL = (R * R * R + kTileThreads - 1) / kTileThreads;
-    T v[NL];
+    const TilePos<R, NP> p(ra, rb, rc);
+    const int tid = (int)threadIdx.x, a = ra + p.aa, b = rb + p.bb;
+    const bool live = p.aa < R && a >= 0 && a < f.nr && b >= 0 && b < f.nt;
+    const int ro = a * f.rowlen + b * f.nh, P = (int)f.P;
+    T bw[2][NP], xv[2][NP]; // [colour][pair]
 #pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const int i = tid + k * kTileThreads;
-        const int cc = i % R, bb = (i / R) % R, aa = i / (R * R);
-        const int a = ra + aa, b = rb + bb;
-        v[k] = T(0);
-        if (i < R * R * R && a >= 0 && a < f.nr && b >= 0 && b < f.nt)
-            v[k] = bv[tile_at(f, a, b, wrapi(rc + cc, f.np))];
-    }
+    for (int u = 0; u < NP; ++u)
 #pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const int i = tid + k * kTileThreads;
-        if (i < R * R * R) {
-            sh.b[i] = v[k];
-            sh.x[i] = T(0);
+        for (int q = 0; q < 2; ++q) {
+            const int cg = wrap_near(rc + 2 * (p.j + u * STEP) + (p.red ^ q), f.np);
+            bw[q][u] = T(0);
+            if (live) bw[q][u] = bv[ro + (cg & 1) * P + (cg >> 1)];
         }
-    }
-    for (int i = tid; i < R * R; i += nt) {
-        const int a = ra + i / R, b = rb + i % R;
-        if (a >= 0 && a < f.nr && b >= 0 && b < f.nt) tile_metrics(f, G, gk, a, b, sh.m[i]);
-        else
-            for (int q = 0; q < 6; ++q) sh.m[i][q] = T(0);
+    const TileRow<T> m = tile_row<T>(f, G, gk, a, b, live);
+    // the first pass from zero reads no neighbour: x = b / D on the red cells
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+        sh.x[0][u][tid] = xv[0][u] = bw[0][u] * m.inv;
+        sh.x[1][u][tid] = xv[1][u] = T(0);
     }
     __syncthreads();
-    // colours 0, 1, 0, 1; the first from zero reads no neighbour (shrink 0)
-    for (int k = 0; k < 4; ++k) {
-        tile_pass<T, R>(f, ra, rb, rc, k, k & 1, k == 0, sh.x, sh.b, sh.m);
-        __syncthreads();
-    }
-    // the tile's cells of x
-    for (int i = tid; i < kTile * kTile * kTile; i += nt) {
-        const int cc = i % kTile, bb = (i / kTile) % kTile, aa = i / (kTile * kTile);
-        const int a = A0 + aa, b = B0 + bb;
-        if (a < f.nr && b < f.nt)
-            x[tile_at(f, a, b, C0 + cc)] = sh.x[((aa + H) * R + bb + H) * R + cc + H];
-    }
-    // red residual on the tile +- 1 (black cells and cells past the walls 0)
-    constexpr int Q = kResR;
-    for (int i = tid; i < Q * Q * Q; i += nt) {
-        const int qc = i % Q, qb = (i / Q) % Q, qa = i / (Q * Q);
-        const int aa = qa + H - 1, bb = qb + H - 1, cc = qc + H - 1;
-        const int a = ra + aa, b = rb + bb;
-        T rv = T(0);
-        if (a >= 0 && a < f.nr && b >= 0 && b < f.nt && ((a + b + rc + cc) & 1) == 0) {
-            const int k = (aa * R + bb) * R + cc;
-            const T* mm = sh.m[aa * R + bb];
-            const T u = sh.x[k];
-            const T y = mm[1] * (sh.x[k + R * R] - u) - mm[0] * (u - sh.x[k - R * R]) +
-                        mm[3] * (sh.x[k + R] - u) - mm[2] * (u - sh.x[k - R]) +
-                        mm[4] * (sh.x[k + 1] - u) - mm[4] * (u - sh.x[k - 1]);
-            rv = sh.b[k] - y;
+    tile_pass<1, R, NP>(m, p, 1, xv, bw, sh.x);
+    __syncthreads();
+    tile_pass<0, R, NP>(m, p, 2, xv, bw, sh.x);
+    __syncthreads();
+    tile_pass<1, R, NP>(m, p, 3, xv, bw, sh.x);
+    __syncthreads();
+    // the red residual on the tile +- 1, in place of the red cells in LDS
+    // (which only their own thread still needs); the tile's cells of x
+    if (live && p.rows(H - 1)) {
+        const bool wr = p.rows(H);
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int cg = rc + 2 * (p.j + u * STEP) + (p.red ^ q);
+                if (wr && p.cell(u, q, H) && cg < f.np) x[ro + (cg & 1) * P + (cg >> 1)] = xv[q][u];
+            }
+            if (!p.cell(u, 0, H - 1)) continue;
+            const T* n = &sh.x[1][u][tid];
+            const T v = xv[0][u];
+            const T y = m.rh * (n[R * STEP] - v) - m.rl * (v - n[-R * STEP]) + m.th * (n[STEP] - v) -
+                        m.tl * (v - n[-STEP]) + m.p * ((xv[1][u] - v) + (n[p.dn[0]] - v));
+            sh.x[0][u][tid] = bw[0][u] - y;
         }
-        sh.r[i] = rv;
     }
     __syncthreads();
     // full weighting onto the coarse cells I = A0/2 .. +3 (weights 1 3 3 1
     // over fine 2I-1 .. 2I+2 in each direction, rows and planes clamped at
-    // the walls, phi wrapped), phi first, then theta, then r
-    const T w0 = T(0.25), w1 = T(0.75);
-    const T w[4] = {w0, w1, w1, w0};
+    // the walls, phi wrapped): 16 lanes a coarse cell, one of the 4 x 4 fine
+    // rows each, of which two cells are red
     constexpr int K4 = kTile / 2;
-    T* pphi = sh.b;                 // [Q][Q][K4]: phi sums of the residual box rows
-    T* pth = sh.b + Q * Q * K4;     // [Q][K4][K4]: then theta
-    for (int i = tid; i < Q * Q * K4; i += nt) {
-        const int kk = i % K4, row = i / K4;
-        const T* rr = sh.r + row * Q + 2 * kk; // fine c = C0 + 2kk - 1 .. +2 at box 2kk .. 2kk+3
-        T s = T(0);
-        for (int t = 0; t < 4; ++t) s += w[t] * rr[t];
-        pphi[i] = s;
+    const int q = tid & 15, cell = tid >> 4;
+    const int kk = cell % K4, jj = (cell / K4) % K4, ii = cell / (K4 * K4);
+    const int I = A0 / 2 + ii, J = B0 / 2 + jj, K = C0 / 2 + kk;
+    const bool on = I < c.nr && J < c.nt && K < c.np;
+    const T w0 = T(0.25), w1 = T(0.75);
+    const int qa = q >> 2, qb = q & 3;
+    T sum = T(0);
+    if (on) {
+        const int fa = clampi(2 * I - 1 + qa, f.nr - 1) - ra, fb = clampi(2 * J - 1 + qb, f.nt - 1) - rb;
+        const int rd = (ra + fa + rb + fb + rc) & 1;
+        // fine c = 2K - 1 .. 2K + 2 at cc = 2t .. 2t + 3, t = kk + (H - 1) / 2:
+        // red are the first and third of a row of red parity 0, else the
+        // second and fourth
+        const int t0 = kk + (H - 1) / 2, t1 = t0 + 1, row = fa * R + fb;
+        const T* r = &sh.x[0][0][row * STEP];
+        const T r0 = r[t0 / STEP * kTileThreads + t0 % STEP];
+        const T r1 = r[t1 / STEP * kTileThreads + t1 % STEP];
+        const T ph = (rd ? w1 : w0) * r0 + (rd ? w0 : w1) * r1;
+        sum = ((qa == 0 || qa == 3 ? w0 : w1) * (qb == 0 || qb == 3 ? w0 : w1)) * ph;
     }
-    __syncthreads();
-    for (int i = tid; i < Q * K4 * K4; i += nt) {
-        const int kk = i % K4, jj = (i / K4) % K4, qa = i / (K4 * K4);
-        const int J = B0 / 2 + jj;
-        T s = T(0);
-        for (int q = 0; q < 4; ++q) {
-            const int b = clampi(2 * J - 1 + q, f.nt - 1); // fine row, mirrored at the walls
-            s += w[q] * pphi[(qa * Q + (b - B0 + 1)) * K4 + kk];
-        }
-        pth[i] = s;
-    }
-    __syncthreads();
-    for (int i = tid; i < K4 * K4 * K4; i += nt) {
-        const int kk = i % K4, jj = (i / K4) % K4, ii = i / (K4 * K4);
-        const int I = A0 / 2 + ii, J = B0 / 2 + jj, K = C0 / 2 + kk;
-        if (I >= c.nr || J >= c.nt) continue;
-        T s = T(0);
-        for (int p = 0; p < 4; ++p) {
-            const int a = clampi(2 * I - 1 + p, f.nr - 1);
-            s += w[p] * pth[((a - A0 + 1) * K4 + jj) * K4 + kk];
-        }
-        bc[tile_at(c, I, J, K)] = s;
-    }
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) sum += __shfl_xor(sum, d);
+    if (on && q == 0) bc[tile_at(c, I, J, K)] = sum;
 }
 
 // Post: xo = 2 red-black sweeps (colours 1, 0, 1, 0) of A x = b from
-// xi + P e on the tile's cells.
+// xi + P e on the tile's cells.  The first pass overwrites every black cell
+// unread, so only xi's red cells are read and corrected.  Returns the
+// thread's part of the sum of b . xo.
 template <typename T>
-__device__ __forceinline__ void d_vpost_tile(Blk bk, Geo f, const T* __restrict__ G, long long gk,
-                                             const T* __restrict__ bv, const T* __restrict__ xi,
-                                             T* __restrict__ xo, Geo c, const T* __restrict__ e,
-                                             TilePostLds<T>& sh)
+__device__ __forceinline__ double d_vpost_tile(Blk bk, Geo f, const T* __restrict__ G, long long gk,
+                                               const T* __restrict__ bv, const T* __restrict__ xi,
+                                               T* __restrict__ xo, Geo c, const T* __restrict__ e,
+                                               TilePostLds<T>& sh)
 {
-    constexpr int R = kPostR, H = kPostHalo, E = kCoarseR;
-    if ((int)bk.L >= tile_count(f)) return; // whole block
+    constexpr int R = kPostR, H = kPostHalo, E = kCoarseR, NP = 2, STEP = TilePos<R, NP>::STEP;
+    static_assert(R * R * STEP == kTileThreads && E * E * E <= kTileThreads, "threads of a tile");
+    if ((int)bk.L >= tile_count(f)) return 0.0; // whole block
     int A0, B0, C0;
     tile_origin(f, (int)bk.L, A0, B0, C0);
     const int ra = A0 - H, rb = B0 - H, rc = C0 - H;
     // coarse box: I = A0/2 - 3 .. A0/2 + 6 (rows and planes clamped, phi wrapped)
     const int ea = A0 / 2 - 3, eb = B0 / 2 - 3, ec = C0 / 2 - 3;
-    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
-    // loads before stores, as in pre
-    constexpr int NE = (E * E * E + kTileThreads - 1) / kTileThreads;
-    constexpr int NX = (R * R * R + kTileThreads - 1) / kTileThreads;
-    T ev[NE], xv[NX], bw[NX];
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-        const int i = tid + k * kTileThreads;
-        const int kc = i % E, kb = (i / E) % E, ka = i / (E * E);
-        ev[k] = i < E * E * E ? e[tile_at(c, clampi(ea + ka, c.nr - 1), clampi(eb + kb, c.nt - 1),
-                                           wrapi(ec + kc, c.np))]
-                              : T(0);
+    const TilePos<R, NP> p(ra, rb, rc);
+    const int tid = (int)threadIdx.x, a = ra + p.aa, b = rb + p.bb;
+    const bool live = a >= 0 && a < f.nr && b >= 0 && b < f.nt;
+    const int ro = a * f.rowlen + b * f.nh, P = (int)f.P;
+    T ev = T(0);
+    if (tid < E * E * E) {
+        const int kc = tid % E, kb = (tid / E) % E, ka = tid / (E * E);
+        const int cg = wrap_near(ec + kc, c.np);
+        ev = e[(cg & 1) * (int)c.P + clampi(ea + ka, c.nr - 1) * c.rowlen +
+               clampi(eb + kb, c.nt - 1) * c.nh + (cg >> 1)];
     }
+    T bw[2][NP], xv[2][NP], xr[NP];
 #pragma unroll
-    for (int k = 0; k < NX; ++k) {
-        const int i = tid + k * kTileThreads;
-        const int cc = i % R, bb = (i / R) % R, aa = i / (R * R);
-        const int a = ra + aa, b = rb + bb;
-        xv[k] = T(0);
-        bw[k] = T(0);
-        if (i < R * R * R && a >= 0 && a < f.nr && b >= 0 && b < f.nt) {
-            const long long o = tile_at(f, a, b, wrapi(rc + cc, f.np));
-            xv[k] = xi[o];
-            bw[k] = bv[o];
+    for (int u = 0; u < NP; ++u) {
+        xr[u] = bw[0][u] = bw[1][u] = T(0);
+        if (live) {
+            // rc is even: a pair's two cells are at one index of both planes
+            const int o = ro + (wrap_near(rc + 2 * (p.j + u * STEP), f.np) >> 1);
+            const int or_ = o + (p.red ? P : 0), ob = o + (p.red ? 0 : P);
+            bw[0][u] = bv[or_];
+            bw[1][u] = bv[ob];
+            xr[u] = xi[or_];
         }
     }
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-        const int i = tid + k * kTileThreads;
-        if (i < E * E * E) sh.e[i] = ev[k];
-    }
-    for (int i = tid; i < R * R; i += nt) {
-        const int a = ra + i / R, b = rb + i % R;
-        if (a >= 0 && a < f.nr && b >= 0 && b < f.nt) tile_metrics(f, G, gk, a, b, sh.m[i]);
-        else
-            for (int q = 0; q < 6; ++q) sh.m[i][q] = T(0);
-    }
+    const TileRow<T> m = tile_row<T>(f, G, gk, a, b, live);
+    if (tid < E * E * E) sh.e[tid] = ev;
     __syncthreads();
     const T w0 = T(0.75), w1 = T(0.25);
+    // fine 2I takes 3/4 of coarse I and 1/4 of I - 1, fine 2I + 1 of I and
+    // I + 1, in each direction: theta, then phi, then r
+    const int da = (a & 1) ? E * E : -E * E, db = (b & 1) ? E : -E, dc = p.red ? 1 : -1;
+    const T* e0 = sh.e + ((a >> 1) - ea) * E * E + ((b >> 1) - eb) * E + rc / 2 - ec + p.j;
 #pragma unroll
-    for (int k = 0; k < NX; ++k) {
-        const int i = tid + k * kTileThreads;
-        if (i >= R * R * R) continue;
-        const int cc = i % R, bb = (i / R) % R, aa = i / (R * R);
-        const int a = ra + aa, b = rb + bb, cg = rc + cc;
-        T xn = T(0);
-        if (a >= 0 && a < f.nr && b >= 0 && b < f.nt) {
-            // fine 2I takes 3/4 of coarse I and 1/4 of I - 1, fine 2I + 1 of
-            // I and I + 1, in each direction: theta, then phi, then r
-            const int I = a >> 1, J = b >> 1, K = cg >> 1; // cg may be negative: floor
-            const int ka = I - ea, kb = J - eb, kc = K - ec;
-            const int da = (a & 1) ? 1 : -1, db = (b & 1) ? 1 : -1, dc = (cg & 1) ? 1 : -1;
+    for (int u = 0; u < NP; ++u) {
+        T v = T(0);
+        if (live) {
+            const T* ee = e0 + u * STEP;
             T tr[2];
+#pragma unroll
             for (int pa = 0; pa < 2; ++pa) {
-                const int ia = ka + (pa ? da : 0);
                 T tp[2];
+#pragma unroll
                 for (int pc = 0; pc < 2; ++pc) {
-                    const int ic = kc + (pc ? dc : 0);
-                    const T* ee = sh.e + ia * E * E + ic;
-                    tp[pc] = w0 * ee[kb * E] + w1 * ee[(kb + db) * E];
+                    const T* q = ee + (pa ? da : 0) + (pc ? dc : 0);
+                    tp[pc] = w0 * q[0] + w1 * q[db];
                 }
                 tr[pa] = w0 * tp[0] + w1 * tp[1];
             }
-            xn = xv[k] + (w0 * tr[0] + w1 * tr[1]);
+            v = xr[u] + (w0 * tr[0] + w1 * tr[1]);
         }
-        sh.x[i] = xn;
-        sh.b[i] = bw[k];
+        sh.x[0][u][tid] = xv[0][u] = v;
+        sh.x[1][u][tid] = xv[1][u] = T(0);
     }
     __syncthreads();
     // colours 1, 0, 1, 0, each on a region one cell smaller
-    for (int k = 0; k < 4; ++k) {
-        tile_pass<T, R>(f, ra, rb, rc, k + 1, 1 - (k & 1), false, sh.x, sh.b, sh.m);
-        __syncthreads();
+    tile_pass<1, R, NP>(m, p, 1, xv, bw, sh.x);
+    __syncthreads();
+    tile_pass<0, R, NP>(m, p, 2, xv, bw, sh.x);
+    __syncthreads();
+    tile_pass<1, R, NP>(m, p, 3, xv, bw, sh.x);
+    __syncthreads();
+    tile_pass<0, R, NP>(m, p, 4, xv, bw, sh.x);
+    double dot = 0.0;
+    if (live && p.rows(H)) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const int cc = 2 * (p.j + u * STEP);
+            if (cc < H || cc >= R - H || rc + cc >= f.np) continue;
+            const int o = ro + ((rc + cc) >> 1);
+            xo[o + (p.red ? P : 0)] = xv[0][u];
+            xo[o + (p.red ? 0 : P)] = xv[1][u];
+            dot = __builtin_fma((double)bw[0][u], (double)xv[0][u], dot);
+            dot = __builtin_fma((double)bw[1][u], (double)xv[1][u], dot);
+        }
     }
-    for (int i = tid; i < kTile * kTile * kTile; i += nt) {
-        const int cc = i % kTile, bb = (i / kTile) % kTile, aa = i / (kTile * kTile);
-        const int a = A0 + aa, b = B0 + bb;
-        if (a < f.nr && b < f.nt)
-            xo[tile_at(f, a, b, C0 + cc)] = sh.x[((aa + H) * R + bb + H) * R + cc + H];
-    }
+    return dot;
 }
 
 template <typename T>
@@ -380,10 +421,23 @@ __global__ void __launch_bounds__(kTileThreads) k_vpost_tile(Geo f, const T* __r
                                                              const T* __restrict__ bv,
                                                              const T* __restrict__ xi,
                                                              T* __restrict__ xo, Geo c,
-                                                             const T* __restrict__ e)
+                                                             const T* __restrict__ e,
+                                                             double* __restrict__ partial)
 {
     __shared__ TilePostLds<T> sh;
-    d_vpost_tile<T>(self_blk(), f, G, gk, bv, xi, xo, c, e, sh);
+    const double dot = d_vpost_tile<T>(self_blk(), f, G, gk, bv, xi, xo, c, e, sh);
+    if (partial) {
+        __shared__ double s[kTileThreads / 64];
+        const double w = wave_sum(dot);
+        const int tid = (int)threadIdx.x;
+        if ((tid & 63) == 0) s[tid >> 6] = w;
+        __syncthreads();
+        if (tid == 0) {
+            double t = 0.0;
+            for (int i = 0; i < kTileThreads / 64; ++i) t += s[i];
+            partial[blockIdx.x] = t;
+        }
+    }
 }
 
 // Batched forms: one block per (problem, tile) of the work table.

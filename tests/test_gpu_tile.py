@@ -1,0 +1,64 @@
+"""The tile path of small levels (csrc/tile.hpp: 8 x 8 x 8 tiles, the V-cycle's
+work on a level in two launches) against the oracle's multigrid, where rings
+and walls cut its tiles, and the batched form's bits against the single
+solve's."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2305_17875_amd import cps, inputs
+from paper_2305_17875_amd.inputs import Shell
+from gpu_util import needs_gpu, log, dev, host, rel, torch
+
+pytestmark = [pytest.mark.gpu, needs_gpu]
+
+SHAPES = [
+    (20, 24, 36),   # the last tile of a ring and of the radial direction half full
+    (8, 8, 12),     # a ring shorter than a tile's box, which wraps onto it
+    (4, 4, 8),      # one tile, half full in two directions
+    (6, 10, 68),    # tiles cut at 6 of 8 planes and 2 of 8 rows; ring remainder 4
+    (16, 16, 2048), # a long ring, the most cells of FP32's limit
+    (80, 96, 144),  # levels of 138240 (beyond 2^16: rows of part wavefronts) and 17280 cells
+]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_one_iteration_matches_oracle(shape, precision):
+    """One iteration of conjugate gradients from zero, x = alpha V(b), with at
+    least two levels: FP64 to 1e-11 (a V-cycle's sums in another order); FP32
+    cycles to 2e-5 (about 20 passes and transfers a level of ~10 roundings of
+    6e-8)."""
+    n_levels = 2 if shape[0] * shape[1] * shape[2] < 1 << 15 else 0
+    g = Shell(*shape, radial_stretch=1.0)
+    b = inputs.smoothed_noise(shape, 33)
+    s = cps.Solver(g, precision=precision, max_iters=1, n_levels=n_levels,
+                   stream=torch.cuda.Stream())
+    try:
+        x = host(s.solve(dev(b).flatten()).p).reshape(shape)
+    finally:
+        s.close()
+    want = O.Multigrid(g, n_levels=n_levels).solve(b, tol=1e-300, max_iters=1, accel=1)[0]
+    err = rel(x, want)
+    log("tile", shape, precision, err)
+    assert err < (1e-11 if precision == 0 else 2e-5)
+
+
+def test_batch_equals_alone():
+    grids = [Shell(*s, radial_stretch=1.0) for s in SHAPES[:4]]
+    rhs = [dev(inputs.smoothed_noise(g.shape, 50 + i)).flatten() for i, g in enumerate(grids)]
+    B = cps.Batch(grids, smoother=0)
+    try:
+        st, p, infos = B.solve(rhs)
+    finally:
+        B.close()
+    assert st == cps.CPS_OK
+    for g, b, x, info in zip(grids, rhs, p, infos):
+        s = cps.Solver(g, precision=1, smoother=0)
+        try:
+            r = s.solve(b)
+        finally:
+            s.close()
+        log("tile batch", g.shape, info.iterations, r.iterations)
+        assert info.iterations == r.iterations
+        assert np.array_equal(host(x), host(r.p)), g.shape
