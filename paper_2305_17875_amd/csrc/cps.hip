@@ -512,6 +512,20 @@ long long smooth(cps_handle* h, int l, const T* b, T* x, int sweeps, bool revers
                 plane_half_sweep<T>(h, l, reverse ? 1 - k : k, b, x, from_zero && s == 0 && k == 0);
         return 0;
     }
+    if (h->ncol == 4 && sweeps == 2 && sweep_fits(h->lv[l].geo) && rl<T>(h, l)) {
+        // a launch a sweep, x -> the residual's buffer -> x
+        const Level<T> L = view<T>(h, l);
+        T* y = rl<T>(h, l);
+        ProfScope ps(h, CPS_KERNEL_GS, l, sweeps * h->ncol);
+        dispatch(h->mode, h->axi, [&](auto M, auto A) {
+            auto k = k_sweep_tile<T, decltype(M)::value, decltype(A)::value>;
+            const int nb = tile_count(L.g), rev = reverse ? 1 : 0;
+            k<<<nb, kSweepThreads, 0, h->stream>>>(L.g, L.G, L.gk, b, x, y, rev, from_zero ? 1 : 0);
+            k<<<nb, kSweepThreads, 0, h->stream>>>(L.g, L.G, L.gk, b, y, x, rev, 0);
+        });
+        LAUNCH_CHECK();
+        return 0;
+    }
     const bool skip = from_zero && h->ncol == 2;
     if (from_zero && !skip) fill<T>(h, x, h->lv[l].n, T(0));
     long long parts = 0;

@@ -123,6 +123,91 @@ struct Delta {
 // Gauss-Seidel update x_c = (b_c - S) / D never loads the old x_c.  The flux
 // form (differences first) is kept for residuals, whose value is small next
 // to D x_c near convergence.
+// The metrics of a cell's six faces (low and high of each direction; pq: the
+// cross term of face p in direction q), from the metric indices of its low
+// faces (ci) and of its r, theta and phi high ones; zero on the high walls.
+template <typename T>
+struct FaceMetrics {
+    T grl, grh, gtl, gth, gpl, gph;
+    T grt_l, grt_h, gtr_l, gtr_h;
+    T grp_l, grp_h, gtp_l, gtp_h, gpr_l, gpr_h, gpt_l, gpt_h;
+};
+
+template <typename T, int MODE>
+__device__ __forceinline__ FaceMetrics<T> face_metrics(const T* __restrict__ G, long long gk,
+                                                       long long ci, long long cr, long long ct,
+                                                       long long cp, bool rhi, bool thi)
+{
+    FaceMetrics<T> m;
+    m.grl = G[ci];
+    m.grh = rhi ? G[cr] : T(0);
+    m.gtl = G[4 * gk + ci];
+    m.gth = thi ? G[4 * gk + ct] : T(0);
+    m.gpl = G[8 * gk + ci];
+    m.gph = G[8 * gk + cp];
+    if constexpr (MODE != MODE_ORTHO) {
+        m.grt_l = G[gk + ci];
+        m.grt_h = rhi ? G[gk + cr] : T(0);
+        m.gtr_l = G[3 * gk + ci];
+        m.gtr_h = thi ? G[3 * gk + ct] : T(0);
+    }
+    if constexpr (MODE == MODE_FULL) {
+        m.grp_l = G[2 * gk + ci];
+        m.grp_h = rhi ? G[2 * gk + cr] : T(0);
+        m.gtp_l = G[5 * gk + ci];
+        m.gtp_h = thi ? G[5 * gk + ct] : T(0);
+        m.gpr_l = G[6 * gk + ci];
+        m.gpr_h = G[6 * gk + cp];
+        m.gpt_l = G[7 * gk + ci];
+        m.gpt_h = G[7 * gk + cp];
+    }
+    return m;
+}
+
+// apply_cell's sum over the neighbours of the cell at i0 of X, the offsets to
+// them given (0 where a wall mirrors the read)
+template <typename T, int MODE, bool OFFDIAG, typename I, typename Acc>
+__device__ __forceinline__ T stencil_sum(const FaceMetrics<T>& m, const Acc& X, I i0, I ra, I rb,
+                                         I ta, I tb, I pa, I pb, T& D)
+{
+    D = -(m.grl + m.grh + m.gtl + m.gth + m.gpl + m.gph);
+    const T xrm = X(i0 + ra), xrp = X(i0 + rb);
+    const T xtm = X(i0 + ta), xtp = X(i0 + tb);
+    const T xpm = X(i0 + pa), xpp = X(i0 + pb);
+    T acc;
+    if constexpr (OFFDIAG) {
+        acc = m.grh * xrp + m.grl * xrm + m.gth * xtp + m.gtl * xtm + m.gph * xpp + m.gpl * xpm;
+    } else {
+        const T x0 = X(i0);
+        acc = m.grh * (xrp - x0) - m.grl * (x0 - xrm) + m.gth * (xtp - x0) - m.gtl * (x0 - xtm) +
+              m.gph * (xpp - x0) - m.gpl * (x0 - xpm);
+    }
+    if constexpr (MODE != MODE_ORTHO) {
+        const T q = T(0.25);
+        const T xrmtm = X(i0 + ra + ta), xrmtp = X(i0 + ra + tb);
+        const T xrptm = X(i0 + rb + ta), xrptp = X(i0 + rb + tb);
+        // r-flux, q = theta
+        acc += q * m.grt_h * (xrptp + xtp - xrptm - xtm) - q * m.grt_l * (xtp + xrmtp - xtm - xrmtm);
+        // theta-flux, q = r
+        acc += q * m.gtr_h * (xrptp + xrp - xrmtp - xrm) - q * m.gtr_l * (xrp + xrptm - xrm - xrmtm);
+        if constexpr (MODE == MODE_FULL) {
+            const T xrmpm = X(i0 + ra + pa), xrmpp = X(i0 + ra + pb);
+            const T xrppm = X(i0 + rb + pa), xrppp = X(i0 + rb + pb);
+            const T xtmpm = X(i0 + ta + pa), xtmpp = X(i0 + ta + pb);
+            const T xtppm = X(i0 + tb + pa), xtppp = X(i0 + tb + pb);
+            // r-flux, q = phi
+            acc += q * m.grp_h * (xrppp + xpp - xrppm - xpm) - q * m.grp_l * (xpp + xrmpp - xpm - xrmpm);
+            // theta-flux, q = phi
+            acc += q * m.gtp_h * (xtppp + xpp - xtppm - xpm) - q * m.gtp_l * (xpp + xtmpp - xpm - xtmpm);
+            // phi-flux, q = r
+            acc += q * m.gpr_h * (xrppp + xrp - xrmpp - xrm) - q * m.gpr_l * (xrp + xrppm - xrm - xrmpm);
+            // phi-flux, q = theta
+            acc += q * m.gpt_h * (xtppp + xtp - xtmpp - xtm) - q * m.gpt_l * (xtp + xtppm - xtm - xtmpm);
+        }
+    }
+    return acc;
+}
+
 template <typename T, int MODE, bool AXI, bool OFFDIAG = false, typename Acc>
 __device__ __forceinline__ T apply_cell(const Geo& g, const T* __restrict__ G, long long gk,
                                         const Acc& X, int a, int b, int s, int j, T& D)
@@ -155,60 +240,10 @@ __device__ __forceinline__ T apply_cell(const Geo& g, const T* __restrict__ G, l
         ct = i0 + st;
         cp = ipp;
     }
-    const T grl = G[ci];
-    const T grh = rhi ? G[cr] : T(0);
-    const T gtl = G[4 * gk + ci];
-    const T gth = thi ? G[4 * gk + ct] : T(0);
-    const T gpl = G[8 * gk + ci];
-    const T gph = G[8 * gk + cp];
-    D = -(grl + grh + gtl + gth + gpl + gph);
     const long long ra = a > 0 ? -sr : 0, rb = rhi ? sr : 0;
     const long long ta = b > 0 ? -st : 0, tb = thi ? st : 0;
-    const T xrm = X(i0 + ra), xrp = X(i0 + rb);
-    const T xtm = X(i0 + ta), xtp = X(i0 + tb);
-    const T xpm = X(i0 + pa), xpp = X(i0 + pb);
-    T acc;
-    if constexpr (OFFDIAG) {
-        acc = grh * xrp + grl * xrm + gth * xtp + gtl * xtm + gph * xpp + gpl * xpm;
-    } else {
-        const T x0 = X(i0);
-        acc = grh * (xrp - x0) - grl * (x0 - xrm) + gth * (xtp - x0) - gtl * (x0 - xtm) +
-              gph * (xpp - x0) - gpl * (x0 - xpm);
-    }
-    if constexpr (MODE != MODE_ORTHO) {
-        const T q = T(0.25);
-        const T xrmtm = X(i0 + ra + ta), xrmtp = X(i0 + ra + tb);
-        const T xrptm = X(i0 + rb + ta), xrptp = X(i0 + rb + tb);
-        const T grt_l = G[gk + ci];
-        const T grt_h = rhi ? G[gk + cr] : T(0);
-        const T gtr_l = G[3 * gk + ci];
-        const T gtr_h = thi ? G[3 * gk + ct] : T(0);
-        // r-flux, q = theta
-        acc += q * grt_h * (xrptp + xtp - xrptm - xtm) - q * grt_l * (xtp + xrmtp - xtm - xrmtm);
-        // theta-flux, q = r
-        acc += q * gtr_h * (xrptp + xrp - xrmtp - xrm) - q * gtr_l * (xrp + xrptm - xrm - xrmtm);
-        if constexpr (MODE == MODE_FULL) {
-            const T xrmpm = X(i0 + ra + pa), xrmpp = X(i0 + ra + pb);
-            const T xrppm = X(i0 + rb + pa), xrppp = X(i0 + rb + pb);
-            const T xtmpm = X(i0 + ta + pa), xtmpp = X(i0 + ta + pb);
-            const T xtppm = X(i0 + tb + pa), xtppp = X(i0 + tb + pb);
-            const T grp_l = G[2 * gk + ci];
-            const T grp_h = rhi ? G[2 * gk + cr] : T(0);
-            const T gtp_l = G[5 * gk + ci];
-            const T gtp_h = thi ? G[5 * gk + ct] : T(0);
-            const T gpr_l = G[6 * gk + ci], gpr_h = G[6 * gk + cp];
-            const T gpt_l = G[7 * gk + ci], gpt_h = G[7 * gk + cp];
-            // r-flux, q = phi
-            acc += q * grp_h * (xrppp + xpp - xrppm - xpm) - q * grp_l * (xpp + xrmpp - xpm - xrmpm);
-            // theta-flux, q = phi
-            acc += q * gtp_h * (xtppp + xpp - xtppm - xpm) - q * gtp_l * (xpp + xtmpp - xpm - xtmpm);
-            // phi-flux, q = r
-            acc += q * gpr_h * (xrppp + xrp - xrmpp - xrm) - q * gpr_l * (xrp + xrppm - xrm - xrmpm);
-            // phi-flux, q = theta
-            acc += q * gpt_h * (xtppp + xtp - xtmpp - xtm) - q * gpt_l * (xtp + xtppm - xtm - xtmpm);
-        }
-    }
-    return acc;
+    return stencil_sum<T, MODE, OFFDIAG>(face_metrics<T, MODE>(G, gk, ci, cr, ct, cp, rhi, thi), X,
+                                         i0, ra, rb, ta, tb, pa, pb, D);
 }
 
 // ---------------------------------------------------------------------------

@@ -470,4 +470,115 @@ __global__ void __launch_bounds__(kTileThreads) kb_vpost_tile(const BItem* __res
                     c.g, c.tile ? c.xt : c.x, sh);
 }
 
+// A four-colour Gauss-Seidel sweep (operators with cross terms) of a small
+// level in one launch, out of place: a block owns an 8 x 8 x 8 tile, loads it
+// with a halo of 4 into LDS and makes the four colour passes, each on a region
+// one cell smaller; halo cells are recomputed by every tile that loads them.
+// A thread takes at most one cell of a pass, and loads its metrics and right-
+// hand side one pass ahead.  The arithmetic of a cell is that of the colour
+// passes (stencil_sum), so the bits are too.  zero: xi is taken as zero and
+// not read.  rev: colours 3 .. 0.
+// Bound by the chain of its loads and passes.  Measured, FP32 with 19 points,
+// against four launches a sweep: 32 x 32 x 64 17.6 -> 10.2 us, 16 x 16 x 32
+// 16.8 -> 8.4; 64 x 64 x 128 21 -> 35 (its 2.9-fold reads of the metrics, in
+// pieces of seven cells, then count), so the line lies between.
+constexpr int kSweepThreads = 704, kSweepHalo = 4, kSweepR = kTile + 2 * kSweepHalo;
+constexpr long long kSweepMaxCells = 1LL << 17;
+
+__host__ __device__ inline bool sweep_fits(const Geo& g)
+{
+    return 2 * g.P <= kSweepMaxCells;
+}
+
+// a thread's cell of one pass: its place in LDS (-1: none), the domain's ends
+template <typename T>
+struct SweepCell {
+    int at;
+    bool rlo, rhi, tlo, thi;
+    T b;
+    FaceMetrics<T> m;
+};
+
+// cell i of pass k, the colour's cells of the region [k + 1, R - k - 1)^3
+template <typename T, int MODE, bool AXI>
+__device__ __forceinline__ SweepCell<T> sweep_cell(const Geo& g, const T* __restrict__ G,
+                                                   long long gk, const T* __restrict__ bv, int ra,
+                                                   int rb, int rc, int k, int rev)
+{
+    constexpr int R = kSweepR;
+    const int s = k + 1, n = R - 2 * s, hn = n / 2, i = (int)threadIdx.x;
+    const int colour = rev ? 3 - k : k, k1 = colour >> 1, k0 = colour & 1;
+    const int aa = s + i / (hn * hn), a = ra + aa;
+    // the colour's theta rows and, of them, cells (d_gs)
+    const int bb = s + 2 * (i / hn % hn) + ((k0 + k1 + a + rb + s) & 1), b = rb + bb;
+    const int cc = s + 2 * (i % hn) + ((k1 + a + rc + s) & 1);
+    SweepCell<T> c;
+    c.at = -1;
+    c.rlo = a > 0;
+    c.rhi = a < g.nr - 1;
+    c.tlo = b > 0;
+    c.thi = b < g.nt - 1;
+    if (i >= n * hn * hn || a < 0 || a >= g.nr || b < 0 || b >= g.nt) return c;
+    c.at = (aa * R + bb) * R + cc;
+    const int cg = wrap_near(rc + cc, g.np), j = cg >> 1, P = (int)g.P;
+    const int row = a * g.rowlen + b * g.nh;
+    const int i0 = (cg & 1) * P + row + j;
+    if (AXI) {
+        const long long ci = a * g.nt + b;
+        c.m = face_metrics<T, MODE>(G, gk, ci, ci + g.nt, ci + 1, ci, c.rhi, c.thi);
+    } else {
+        const int cp = (cg & 1) == 0 ? P + row + j : row + (j == g.nh - 1 ? 0 : j + 1);
+        c.m = face_metrics<T, MODE>(G, gk, i0, i0 + g.rowlen, i0 + g.nh, cp, c.rhi, c.thi);
+    }
+    c.b = bv[i0];
+    return c;
+}
+
+template <typename T, int MODE, bool AXI>
+__global__ void __launch_bounds__(kSweepThreads)
+    k_sweep_tile(Geo g, const T* __restrict__ G, long long gk, const T* __restrict__ bv,
+                 const T* __restrict__ xi, T* __restrict__ xo, int rev, int zero)
+{
+    constexpr int R = kSweepR, H = kSweepHalo, NX = (R * R * R + kSweepThreads - 1) / kSweepThreads;
+    static_assert((R - 2) * (R / 2 - 1) * (R / 2 - 1) <= kSweepThreads, "cells of the first pass");
+    __shared__ T X[NX * kSweepThreads];
+    int A0, B0, C0;
+    tile_origin(g, (int)xcd_block(), A0, B0, C0);
+    const int ra = A0 - H, rb = B0 - H, rc = C0 - H, tid = (int)threadIdx.x;
+    const int P = (int)g.P;
+    SweepCell<T> c = sweep_cell<T, MODE, AXI>(g, G, gk, bv, ra, rb, rc, 0, rev);
+    T v[NX];
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+        const int i = tid + k * kSweepThreads, a = ra + i / (R * R), b = rb + i / R % R;
+        const int cg = wrap_near(rc + i % R, g.np);
+        v[k] = T(0);
+        if (!zero && i < R * R * R && a >= 0 && a < g.nr && b >= 0 && b < g.nt)
+            v[k] = xi[(cg & 1) * P + a * g.rowlen + b * g.nh + (cg >> 1)];
+    }
+#pragma unroll
+    for (int k = 0; k < NX; ++k) X[tid + k * kSweepThreads] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        SweepCell<T> next;
+        if (k < 3) next = sweep_cell<T, MODE, AXI>(g, G, gk, bv, ra, rb, rc, k + 1, rev);
+        if (c.at >= 0) {
+            T D;
+            const T S = stencil_sum<T, MODE, true>(
+                c.m, [&](int q) { return X[q]; }, c.at, c.rlo ? -R * R : 0, c.rhi ? R * R : 0,
+                c.tlo ? -R : 0, c.thi ? R : 0, -1, 1, D);
+            X[c.at] = (c.b - S) / D;
+        }
+        __syncthreads();
+        if (k < 3) c = next;
+    }
+    if (tid >= kTile * kTile * kTile) return;
+    const int cc = tid % kTile, bb = tid / kTile % kTile, aa = tid / (kTile * kTile);
+    const int a = A0 + aa, b = B0 + bb, cg = C0 + cc;
+    if (a < g.nr && b < g.nt && cg < g.np)
+        xo[(cg & 1) * P + a * g.rowlen + b * g.nh + (cg >> 1)] =
+            X[((aa + H) * R + bb + H) * R + cc + H];
+}
+
 } // namespace cps

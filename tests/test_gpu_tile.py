@@ -7,7 +7,7 @@ import pytest
 
 import oracle as O
 from paper_2305_17875_amd import cps, inputs
-from paper_2305_17875_amd.inputs import Shell
+from paper_2305_17875_amd.inputs import Shell, MAP_OBLATE, MAP_TRIAXIAL
 from gpu_util import needs_gpu, log, dev, host, rel, torch
 
 pytestmark = [pytest.mark.gpu, needs_gpu]
@@ -62,3 +62,29 @@ def test_batch_equals_alone():
         log("tile batch", g.shape, info.iterations, r.iterations)
         assert info.iterations == r.iterations
         assert np.array_equal(host(x), host(r.p)), g.shape
+
+
+SWEEPS = [(20, 24, 36), (8, 8, 12), (4, 4, 8), (6, 10, 68), (32, 32, 128), (32, 32, 136)]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("map_", [MAP_OBLATE, MAP_TRIAXIAL], ids=["oblate", "triaxial"])
+@pytest.mark.parametrize("shape", SWEEPS, ids=lambda s: "x".join(map(str, s)))
+def test_four_colour_sweeps_match_oracle(shape, map_, precision):
+    """Operators with cross terms, point smoother: a launch a sweep up to 2^17
+    cells (32 x 32 x 128), tiles cut by rings and walls; above it a launch a
+    colour.  Bounds as test_one_iteration_matches_oracle with twice the passes:
+    2e-11 and 4e-5."""
+    n_levels = 2 if shape[0] * shape[1] * shape[2] < 1 << 15 else 0
+    g = Shell(*shape, map=map_, flattening=0.1, skew=0.2 if map_ == MAP_TRIAXIAL else 0.0)
+    b = inputs.smoothed_noise(shape, 35)
+    s = cps.Solver(g, precision=precision, max_iters=1, n_levels=n_levels,
+                   stream=torch.cuda.Stream())
+    try:
+        x = host(s.solve(dev(b).flatten()).p).reshape(shape)
+    finally:
+        s.close()
+    want = O.Multigrid(g, n_levels=n_levels).solve(b, tol=1e-300, max_iters=1, accel=1)[0]
+    err = rel(x, want)
+    log("sweep", shape, map_, precision, err)
+    assert err < (2e-11 if precision == 0 else 4e-5)
