@@ -846,6 +846,13 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
     return parts;
 }
 
+// Partial sums that every block of the consuming launch adds up itself, and the
+// most blocks that do so: 8 KB a block from L2 at most, under 1 us, where the
+// launch for a sum takes 2.4 to 4.6 us (32^3: three sums of 64 to 128 parts an
+// iteration; 80 x 96 x 144: 180 and 1080).
+constexpr long long kFoldParts = 2048;
+constexpr int kFoldGrid = 1024;
+
 // out = M^-1 in : one V-cycle from zero, FP64 or FP32 inside (scaled by
 // sc[S_SCALE] so that FP32 sees O(1) values).  rz_slot >= 0: also
 // sc[rz_slot] = in . out; zq: also sc[S_ZQ] = out . zq.  Both are taken
@@ -857,11 +864,14 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
 // and only the dot products are taken.  rz_ops / zq_ops: scalar updates done
 // by the launch that stores r.z / z.q (RED_* of k_reduce_cg).  zero_done
 // (FP64): out already holds the cycle's zero-iterate first pass of in.
+// rz_parts (FP64): the partial sums of r.z may be left in h->partial, not added
+// up; their number (0: S_RZ holds the sum).
 void precondition(cps_handle* h, const double* in, double* out, int rz_slot = -1,
                   const double* zq = nullptr, bool rhs_cast = false, int rz_ops = 0,
-                  int zq_ops = 0, bool zero_done = false)
+                  int zq_ops = 0, bool zero_done = false, long long* rz_parts = nullptr)
 {
     const long long n = h->lv[0].n;
+    if (rz_parts) *rz_parts = 0;
     if (h->opts.precision == 0) {
         long long parts;
         {
@@ -869,7 +879,8 @@ void precondition(cps_handle* h, const double* in, double* out, int rz_slot = -1
             parts = vcycle<double>(h, in, out, true, rz_slot >= 0, zero_done);
         }
         if (rz_slot >= 0) {
-            if (parts) reduce(h, parts, rz_slot, 0, rz_ops);
+            if (parts && rz_parts && parts <= kFoldParts) *rz_parts = parts;
+            else if (parts) reduce(h, parts, rz_slot, 0, rz_ops);
             else dot<double, double>(h, n, in, out, rz_slot, rz_ops);
         }
         if (zq) dot<double, double>(h, n, out, zq, S_ZQ, zq_ops);
@@ -894,8 +905,15 @@ void precondition(cps_handle* h, const double* in, double* out, int rz_slot = -1
         k_cast_dots<<<vg, kBlock, 0, h->stream>>>(n, x, out, h->sc.p, S_SCALE, in, zq,
                                                   h->partial.p, h->partial.p + vg);
         LAUNCH_CHECK();
-        if (rz_slot >= 0) reduce(h, vg, rz_slot, 0, rz_ops);
-        if (zq) reduce(h, vg, S_ZQ, vg, zq_ops);
+        if (rz_slot >= 0 && zq) {
+            k_reduce_cg2<<<1, kBlock, 0, h->stream>>>(h->partial.p, vg, vg, h->sc.p,
+                                                      rz_ops | zq_ops);
+            LAUNCH_CHECK();
+        } else if (rz_slot >= 0) {
+            reduce(h, vg, rz_slot, 0, rz_ops);
+        } else {
+            reduce(h, vg, S_ZQ, vg, zq_ops);
+        }
     }
 }
 
@@ -1562,11 +1580,19 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
             k_copy<double><<<nblk(n), kBlock, 0, h->stream>>>(n, z, p);
             LAUNCH_CHECK();
             reduce(h, apply<double>(h, 0, p, q, p), S_PQ, 0, RED_ALPHA | RED_SHIFT_ALPHA);
-            // the mixed form on the fused path: the step also casts the new
-            // residual into the FP32 right-hand side, and the direction is
-            // formed from the FP32 correction (no FP64 cast pass, z not stored)
+            // the mixed form: the step also casts the new residual into the
+            // FP32 right-hand side; on the fused path the direction is formed
+            // from the FP32 correction (no FP64 cast pass, z not stored)
             const bool cast_fused = fused && mixed;
-            float* r32 = cast_fused ? h->lv[0].b32.p : nullptr;
+            float* r32 = mixed ? h->lv[0].b32.p : nullptr;
+            // the 7-point operator on rings that are no row pairs: the
+            // direction and the product in one launch (k_apply_dir_march), the
+            // iterate updated by the step; in FP64 without launches for the
+            // sums where these are few
+            const bool dirmarch = marching(h) && !fused;
+            const MarchShape dms = stencil_shape(g0);
+            const bool fold = dirmarch && !mixed && dms.grid <= kFoldParts;
+            double* pdot = h->partial.p + h->partial.n / 2; // sums of p.q beside those of r.z
             // FP64: the step forms q = A p again from p, so the direction
             // kernel does not store q (k_cg_step_z).  Point smoothing with the
             // per-kernel finest level: it also makes the next cycle's
@@ -1608,16 +1634,37 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
             for (;;) {
                 while (st == CPS_E_NOT_CONVERGED && it < maxit) {
                     ++it;
-                    const int parity = fused ? (it & 1) : 0;
+                    const int parity = fused || dirmarch ? (it & 1) : 0;
                     double* pc = parity ? pn : p; // direction of the previous iteration
                     double* pnx = parity ? p : pn;
                     run_body(h, G_CG0 + parity, [&] {
                         // the launch that stores the new r.z keeps the old one
                         // and forms beta (flexible: the one that stores z.q)
+                        long long nrz = 0;
                         precondition(h, r, cast_fused ? nullptr : z, S_RZ, flexible ? q : nullptr,
-                                     cast_fused, flexible ? RED_SHIFT_RZ : RED_SHIFT_RZ | RED_BETA,
-                                     flexible ? RED_FBETA : 0, zfused);
-                        if (fused) {
+                                     mixed, flexible ? RED_SHIFT_RZ : RED_SHIFT_RZ | RED_BETA,
+                                     flexible ? RED_FBETA : 0, zfused, fold ? &nrz : nullptr);
+                        if (dirmarch) {
+                            {
+                                ProfScope ps(h, CPS_KERNEL_APPLY, 0);
+                                auto k = g0.nh % 64 == 0 ? k_apply_dir_march<true>
+                                                         : k_apply_dir_march<false>;
+                                k<<<dms.grid, kBlock, 0, h->stream>>>(
+                                    g0, h->lv[0].G64.p, h->lv[0].gk, dms.bpa, dms.ch, z, pc, pnx, q,
+                                    h->sc.p, h->partial.p, nrz, pdot);
+                                LAUNCH_CHECK();
+                            }
+                            if (nrz) {
+                                const int grid = std::min<int>(vgrid(n), kFoldGrid);
+                                k_cg_step_sum<<<grid, kBlock, 0, h->stream>>>(
+                                    n, h->sc.p, x, r, pnx, q, pdot, dms.grid, h->partial.p);
+                                LAUNCH_CHECK();
+                                reduce_norm(h, grid, S_RR);
+                            } else {
+                                reduce(h, dms.grid, S_PQ, h->partial.n / 2, RED_ALPHA);
+                                step(pnx);
+                            }
+                        } else if (fused) {
                             const MarchShape ms = stencil_shape(g0);
                             {
                                 ProfScope ps(h, CPS_KERNEL_APPLY, 0); // the product only
@@ -1675,7 +1722,7 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
                 fill<double>(h, pn, n, 0.0);
                 // the next body expects the zero-iterate pass of the new r
                 if (zfused) gs_pass<double>(h, 0, 0, r, z, true);
-                if (cast_fused) {
+                if (mixed) {
                     k_cast<double, float><<<nblk(n), kBlock, 0, h->stream>>>(n, r, r32, h->sc.p,
                                                                              S_SCALE, 1);
                     LAUNCH_CHECK();

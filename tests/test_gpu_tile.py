@@ -88,3 +88,39 @@ def test_four_colour_sweeps_match_oracle(shape, map_, precision):
     err = rel(x, want)
     log("sweep", shape, map_, precision, err)
     assert err < (2e-11 if precision == 0 else 4e-5)
+
+
+# The outer iteration's launches off the row-pair levels: direction and product
+# in one, sums added up by the blocks that use them (the tile path's and the
+# marching path's r . z), or by launches (a single level and the plane smoother
+# leave no partial sums); rings of whole wavefronts and others.
+OUTER = [((32, 32, 32), 0, 0), ((20, 24, 36), 0, 0), ((80, 96, 144), 0, 0), ((4, 7, 128), 0, 1),
+         ((16, 16, 32), 1, 0)]
+
+
+@pytest.mark.parametrize("shape,smoother,n_levels", OUTER,
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_outer_iterations_match_oracle(shape, smoother, n_levels):
+    """Four iterations of FP64 conjugate gradients, point smoother: to 1e-10 of
+    the oracle's (each iteration's 1e-11 carried on by the later ones); plane
+    smoother and single level: a solve to 1e-10, whose residual the oracle forms
+    of the answer."""
+    g = Shell(*shape, radial_stretch=1.0)
+    b = inputs.smoothed_noise(shape, 36)
+    few = smoother == 0 and n_levels == 0
+    s = cps.Solver(g, precision=0, smoother=smoother, n_levels=n_levels,
+                   max_iters=4 if few else 200, stream=torch.cuda.Stream())
+    try:
+        r = s.solve(dev(b).flatten())
+        x = host(r.p).reshape(shape)
+    finally:
+        s.close()
+    if few:
+        want = O.Multigrid(g).solve(b, tol=1e-300, max_iters=4, accel=1)[0]
+        log("outer", shape, rel(x, want))
+        assert rel(x, want) < 1e-10
+    else:
+        d = b - b.mean()
+        res = np.linalg.norm(O.residual(O.face_metrics(g), d, x)) / np.linalg.norm(d)
+        log("outer", shape, r.iterations, res)
+        assert r.status == cps.CPS_OK and res <= 1.001e-10
