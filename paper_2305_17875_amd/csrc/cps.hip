@@ -220,6 +220,7 @@ struct cps_handle {
     Buf<double> partial;
     Buf<double> sc; // device scalars (S_* slots)
     double* hsc = nullptr; // pinned host mirror
+    hipEvent_t norm_ev[2] = {nullptr, nullptr}; // outer iterations launched ahead
     // level-0 FP64 work vectors
     Buf<double> x0, b0, r, z, pd, q, r0, v, s, t, ph, sh;
     // plane smoother scratch: the spectra of one parity
@@ -238,7 +239,7 @@ struct cps_handle {
     LineBC lf_bc[2] = {};
     bool cm_valid = false;
     // captured outer-iteration bodies (G_* keys), replayed by run_body
-    hipGraphExec_t gexec[4] = {};
+    hipGraphExec_t gexec[6] = {}; // by G_*
     // optional HIP-event timing of the finest-level kernels, per class
     bool prof = false;
     uint32_t prof_mask = ~0u; // kernel classes recorded while prof is on
@@ -647,6 +648,15 @@ void reduce_norm(cps_handle* h, long long nparts, int slot)
     LAUNCH_CHECK();
 }
 
+// the same for an iteration with the next one launched behind it (side: which
+// of the two)
+void reduce_stop(cps_handle* h, long long nparts, int side)
+{
+    k_reduce_stop<<<1, kBlock, 0, h->stream>>>(h->partial.p, nparts, h->sc.p,
+                                               h->hsc + (side ? S_RR_ODD : S_RR));
+    LAUNCH_CHECK();
+}
+
 template <typename T, typename U>
 void dot(cps_handle* h, long long n, const T* u, const U* v, int slot, int ops = 0)
 {
@@ -852,6 +862,8 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
 // iteration; 80 x 96 x 144: 180 and 1080).
 constexpr long long kFoldParts = 2048;
 constexpr int kFoldGrid = 1024;
+// the most cells of a problem whose iterations are launched ahead
+constexpr long long kAheadCells = 1LL << 21;
 
 // out = M^-1 in : one V-cycle from zero, FP64 or FP32 inside (scaled by
 // sc[S_SCALE] so that FP32 sees O(1) values).  rz_slot >= 0: also
@@ -922,7 +934,7 @@ void precondition(cps_handle* h, const double* in, double* out, int rz_slot = -1
 // the handle runs eagerly, is being profiled (per-launch events) or runs on
 // the null stream (which cannot be captured).  A body ends by copying the
 // residual norm to the pinned host mirror; the caller synchronises.
-enum { G_CG0 = 0, G_CG1 = 1, G_BICG = 2, G_RICH = 3 };
+enum { G_CG0 = 0, G_CG1 = 1, G_BICG = 2, G_RICH = 3, G_AHEAD0 = 4, G_AHEAD1 = 5 };
 
 template <typename F>
 void run_body(cps_handle* h, int key, F&& body)
@@ -1467,6 +1479,8 @@ void destroy(cps_handle* h)
     }
     for (auto& v : h->ev)
         for (hipEvent_t e : v) (void)hipEventDestroy(e);
+    for (hipEvent_t e : h->norm_ev)
+        if (e) (void)hipEventDestroy(e);
     delete h;
 }
 
@@ -1479,6 +1493,20 @@ cps_status check_norm(double rr, double bb, double tol, double* rel)
     *rel = std::sqrt(rr / bb);
     if (!std::isfinite(*rel)) return CPS_E_DIVERGED;
     return *rel <= tol ? CPS_OK : CPS_E_NOT_CONVERGED;
+}
+
+// The largest rr that check_norm takes as converged (it is monotone in rr), so
+// that the device compares as the host does; false if a few steps around
+// tol^2 bb do not find it (tolerances near the ends of the range).
+bool stop_norm(double bb, double tol, double* rr)
+{
+    auto ok = [&](double v) { return std::sqrt(v / bb) <= tol; };
+    double t = tol * tol * bb;
+    if (!(t > 1e-290 && t < 1e290 && bb > 1e-290 && bb < 1e290)) return false;
+    for (int k = 0; k < 64 && ok(t); ++k) t = std::nextafter(t, HUGE_VAL);
+    for (int k = 0; k < 64 && !ok(t); ++k) t = std::nextafter(t, 0.0);
+    *rr = t;
+    return ok(t) && !ok(std::nextafter(t, HUGE_VAL));
 }
 
 // The Krylov recurrences update r without forming b - A x, and rounding
@@ -1593,6 +1621,26 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
             const MarchShape dms = stencil_shape(g0);
             const bool fold = dirmarch && !mixed && dms.grid <= kFoldParts;
             double* pdot = h->partial.p + h->partial.n / 2; // sums of p.q beside those of r.z
+            // Small problems with the point smoother (tens of iterations of a
+            // few hundred us at most): the next iteration is launched before
+            // the host reads this one's norm, which hides the read and the
+            // launch (12 to 14 us an iteration); if the norm ends the solve,
+            // the step launched ahead leaves the iterate and the residual as
+            // they are (S_STOP).  That costs one iteration's time a solve, so
+            // large problems, and the plane smoother's few iterations, wait.
+            double stop_rr = 0.0;
+            const bool ahead = !fused && h->opts.smoother == 0 && n <= kAheadCells &&
+                               !h->opts.eager && !h->prof && h->stream &&
+                               stop_norm(bb, tol, &stop_rr);
+            if (ahead) {
+                for (hipEvent_t& e : h->norm_ev)
+                    if (!e) HIPC(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+                k_set_scalar<<<1, 1, 0, h->stream>>>(h->sc.p, S_STOP_RR, stop_rr);
+                k_set_scalar<<<1, 1, 0, h->stream>>>(h->sc.p, S_STOP, 0.0);
+                LAUNCH_CHECK();
+            }
+            int launched = 1; // the last iteration launched
+            int gate = -1;    // inside an iteration that may be ahead: its side
             // FP64: the step forms q = A p again from p, so the direction
             // kernel does not store q (k_cg_step_z).  Point smoothing with the
             // per-kernel finest level: it also makes the next cycle's
@@ -1616,9 +1664,11 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
                     reduce_norm(h, ms.grid, S_RR);
                 } else {
                     k_cg_step<<<vgrid(n), kBlock, 0, h->stream>>>(n, h->sc.p, fused ? nullptr : x,
-                                                                  r, pk, q, h->partial.p, r32);
+                                                                  r, pk, q, h->partial.p, r32,
+                                                                  gate >= 0 ? 1 : 0);
                     LAUNCH_CHECK();
-                    reduce_norm(h, vgrid(n), S_RR);
+                    if (gate >= 0) reduce_stop(h, vgrid(n), gate);
+                    else reduce_norm(h, vgrid(n), S_RR);
                 }
             };
             step(p);
@@ -1632,12 +1682,12 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
             // both (the older direction is still in the buffer it overwrites)
             double* pprev = nullptr; // the direction an even body left pending
             for (;;) {
-                while (st == CPS_E_NOT_CONVERGED && it < maxit) {
-                    ++it;
-                    const int parity = fused || dirmarch ? (it & 1) : 0;
+                auto launch = [&](int k) { // iteration k
+                    const int parity = fused || dirmarch ? (k & 1) : 0;
                     double* pc = parity ? pn : p; // direction of the previous iteration
                     double* pnx = parity ? p : pn;
-                    run_body(h, G_CG0 + parity, [&] {
+                    gate = ahead ? (k & 1) : -1;
+                    run_body(h, ahead ? G_AHEAD0 + (k & 1) : G_CG0 + parity, [&] {
                         // the launch that stores the new r.z keeps the old one
                         // and forms beta (flexible: the one that stores z.q)
                         long long nrz = 0;
@@ -1657,9 +1707,11 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
                             if (nrz) {
                                 const int grid = std::min<int>(vgrid(n), kFoldGrid);
                                 k_cg_step_sum<<<grid, kBlock, 0, h->stream>>>(
-                                    n, h->sc.p, x, r, pnx, q, pdot, dms.grid, h->partial.p);
+                                    n, h->sc.p, x, r, pnx, q, pdot, dms.grid, h->partial.p,
+                                    gate >= 0 ? 1 : 0);
                                 LAUNCH_CHECK();
-                                reduce_norm(h, grid, S_RR);
+                                if (gate >= 0) reduce_stop(h, grid, gate);
+                                else reduce_norm(h, grid, S_RR);
                             } else {
                                 reduce(h, dms.grid, S_PQ, h->partial.n / 2, RED_ALPHA);
                                 step(pnx);
@@ -1699,7 +1751,19 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
                         plast = pnx;
                         pprev = parity ? nullptr : pc;
                     }
-                    st = check_norm(body_norm(h, S_RR), bb, tol, &rel);
+                    if (ahead) HIPC(hipEventRecord(h->norm_ev[k & 1], h->stream));
+                    launched = k;
+                };
+                while (st == CPS_E_NOT_CONVERGED && it < maxit) {
+                    ++it;
+                    if (launched < it) launch(it);
+                    if (!ahead) {
+                        st = check_norm(body_norm(h, S_RR), bb, tol, &rel);
+                        continue;
+                    }
+                    if (it < maxit) launch(it + 1);
+                    HIPC(hipEventSynchronize(h->norm_ev[it & 1]));
+                    st = check_norm(h->hsc[it & 1 ? S_RR_ODD : S_RR], bb, tol, &rel);
                 }
                 if (fused) { // the updates the last steps left pending, in order
                     if (pprev) {
@@ -1720,6 +1784,11 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
                 // product applies with it and the direction before it)
                 fill<double>(h, p, n, 0.0);
                 fill<double>(h, pn, n, 0.0);
+                launched = it; // an iteration ahead has made no step
+                if (ahead) {
+                    k_set_scalar<<<1, 1, 0, h->stream>>>(h->sc.p, S_STOP, 0.0);
+                    LAUNCH_CHECK();
+                }
                 // the next body expects the zero-iterate pass of the new r
                 if (zfused) gs_pass<double>(h, 0, 0, r, z, true);
                 if (mixed) {

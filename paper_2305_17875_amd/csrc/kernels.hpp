@@ -33,7 +33,8 @@ enum { MODE_ORTHO = 0, MODE_RT = 1, MODE_FULL = 2 };
 // device scalar slots of the Krylov solvers (sc[])
 enum {
     S_BB = 0, S_RR, S_RZ, S_RZ_OLD, S_PQ, S_ZQ, S_ALPHA, S_BETA, S_OMEGA, S_RHO, S_RHO_OLD,
-    S_TS, S_TT, S_R0V, S_SUM, S_SCALE, S_ALPHA_OLD, S_RZ_NEW, S_COUNT
+    S_TS, S_TT, S_R0V, S_SUM, S_SCALE, S_ALPHA_OLD, S_RZ_NEW, S_STOP, S_STOP_RR,
+    S_RR_ODD, S_COUNT
 };
 
 constexpr int kBlock = 256;
@@ -2428,6 +2429,19 @@ __global__ void __launch_bounds__(kBlock) k_reduce_cg2(const double* __restrict_
     sc[S_ZQ] = zq;
     if (ops & RED_FBETA) sc[S_BETA] = -sc[S_ALPHA] * sc[S_ZQ] / sc[S_RZ_OLD];
 }
+// The norm of an outer iteration that the host reads after it has launched the
+// next one: S_STOP tells that one's step whether the solve has ended (rr is at
+// most S_STOP_RR, or rr / bb is not finite: what the host's check will find).
+__global__ void __launch_bounds__(kBlock) k_reduce_stop(const double* __restrict__ partial,
+                                                        long long n, double* __restrict__ sc,
+                                                        double* __restrict__ host)
+{
+    const double rr = d_reduce_sum(partial, n);
+    if (threadIdx.x != 0) return;
+    sc[S_RR] = rr;
+    sc[S_STOP] = rr > sc[S_STOP_RR] && rr / sc[S_BB] <= 1.7976931348623157e308 ? 0.0 : 1.0;
+    *host = rr;
+}
 __global__ void k_bicg_beta(double* sc)
 {
     sc[S_BETA] = (sc[S_RHO] / sc[S_RHO_OLD]) * (sc[S_ALPHA] / sc[S_OMEGA]);
@@ -2439,14 +2453,16 @@ __global__ void k_set_scalar(double* sc, int dst, double v) { sc[dst] = v; }
 // sc[S_SCALE] = sqrt(sc[src])
 __global__ void k_sqrt_scalar(double* sc, int dst, int src) { sc[dst] = sqrt(sc[src]); }
 
-// x += alpha p ; r -= alpha q ; partial sums of r^2   (CG step)
+// x += alpha p ; r -= alpha q ; partial sums of r^2   (CG step); go false:
+// the sums only (the solve ended one iteration ago)
 __device__ __forceinline__ void d_cg_step(Blk bk, long long n, const double* __restrict__ sc,
                                                     double* __restrict__ x,
                                                     double* __restrict__ r,
                                                     const double* __restrict__ p,
                                                     const double* __restrict__ q,
                                                     double* __restrict__ partial,
-                                                    float* __restrict__ r32, double al)
+                                                    float* __restrict__ r32, double al,
+                                                    bool go = true)
 {
     // r32: also the FP32 right-hand side of the next mixed-form V-cycle,
     // (float)(r / scale) as k_cast forms it
@@ -2454,10 +2470,13 @@ __device__ __forceinline__ void d_cg_step(Blk bk, long long n, const double* __r
     double acc = 0.0;
     const long long stride = (long long)bk.G * blockDim.x;
     for (long long i = (long long)bk.L * blockDim.x + threadIdx.x; i < n; i += stride) {
-        if (x) x[i] = __builtin_fma(al, p[i], x[i]);
-        const double v = __builtin_fma(-al, q[i], r[i]);
-        r[i] = v;
-        if (r32) r32[i] = (float)(v * inv);
+        double v = r[i];
+        if (go) {
+            if (x) x[i] = __builtin_fma(al, p[i], x[i]);
+            v = __builtin_fma(-al, q[i], v);
+            r[i] = v;
+            if (r32) r32[i] = (float)(v * inv);
+        }
         acc = __builtin_fma(v, v, acc);
     }
     acc = block_sum(acc);
@@ -2470,9 +2489,10 @@ __global__ void __launch_bounds__(kBlock) k_cg_step(long long n, const double* _
                                                     const double* __restrict__ p,
                                                     const double* __restrict__ q,
                                                     double* __restrict__ partial,
-                                                    float* __restrict__ r32)
+                                                    float* __restrict__ r32, int gate)
 {
-    d_cg_step(self_blk(), n, sc, x, r, p, q, partial, r32, sc[S_ALPHA]);
+    d_cg_step(self_blk(), n, sc, x, r, p, q, partial, r32, sc[S_ALPHA],
+              !gate || sc[S_STOP] == 0.0);
 }
 
 // the sum of partial[0 .. n) in every thread of the block
@@ -2496,7 +2516,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_step_sum(long long n, double* sc,
                                                         const double* __restrict__ q,
                                                         const double* __restrict__ ppq,
                                                         long long npq,
-                                                        double* __restrict__ partial)
+                                                        double* __restrict__ partial, int gate)
 {
     const double pq = block_reduce_sum(ppq, npq), rz = sc[S_RZ_NEW], al = rz / pq;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -2504,7 +2524,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_step_sum(long long n, double* sc,
         sc[S_ALPHA] = al;
         sc[S_RZ] = rz;
     }
-    d_cg_step(self_blk(), n, sc, x, r, p, q, partial, nullptr, al);
+    d_cg_step(self_blk(), n, sc, x, r, p, q, partial, nullptr, al, !gate || sc[S_STOP] == 0.0);
 }
 
 // q = A p with the direction p = z + beta p_old formed where it is read (as

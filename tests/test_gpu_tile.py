@@ -124,3 +124,33 @@ def test_outer_iterations_match_oracle(shape, smoother, n_levels):
         res = np.linalg.norm(O.residual(O.face_metrics(g), d, x)) / np.linalg.norm(d)
         log("outer", shape, r.iterations, res)
         assert r.status == cps.CPS_OK and res <= 1.001e-10
+
+
+@pytest.mark.parametrize("shape,map_,precision", [((16, 16, 24), 1, 0), ((16, 16, 24), 1, 1),
+                                                  ((16, 16, 32), MAP_TRIAXIAL, 1)],
+                         ids=["fp64", "mixed", "triaxial"])
+def test_iterations_launched_ahead_leave_no_trace(shape, map_, precision):
+    """A small solve launches an iteration before it has read the last one's
+    norm; the eager form does not.  Iterate, count and residual are the same
+    bits, wherever the solve ends (a norm, the limit, never) and whatever the
+    solve before it on the same handle did."""
+    g = Shell(*shape, map=map_, flattening=0.1 if map_ == MAP_TRIAXIAL else 0.0,
+              skew=0.2 if map_ == MAP_TRIAXIAL else 0.0)
+    side = torch.cuda.Stream()
+    for most in (1, 2, 3, 60):
+        sa, se = (cps.Solver(g, precision=precision, max_iters=most, stream=side, eager=e)
+                  for e in (False, True))
+        try:
+            for k, tol in enumerate((1e-2, 1e-10, 1e-15, 1e-160, 1e-6)):
+                b = dev(inputs.smoothed_noise(shape, 60 + k)).flatten()
+                torch.cuda.synchronize()
+                ra = sa.solve(b, tol=tol)
+                xa = host(ra.p)
+                re = se.solve(b, tol=tol)
+                log("ahead", shape, most, tol, ra.iterations, ra.status)
+                assert (ra.status, ra.iterations, ra.rel_residual) == \
+                    (re.status, re.iterations, re.rel_residual)
+                assert np.array_equal(xa, host(re.p)), (most, tol)
+        finally:
+            sa.close()
+            se.close()
