@@ -231,8 +231,9 @@ void b_vcycle(cps_batch* B, BatchGroup& G)
         if (!G.gs[l].count) continue;
         b_smooth(B, G, l, false, true);
         // as vcycle(): after point red-black smoothing, the red residual on
-        // row-pair levels (the kernels check the level's shape)
-        const int red = !G.plane && G.mode == MODE_ORTHO && G.axi ? 1 : 0;
+        // row-pair levels (the kernels check the level's shape); after plane
+        // smoothing the even rows'
+        const int red = G.plane ? 2 : (G.mode == MODE_ORTHO && G.axi ? 1 : 0);
         dispatch(G.mode, G.axi, [&](auto M, auto A) {
             blaunch(B, G.res[l], kb_residual<float, decltype(M)::value, decltype(A)::value>, l, red);
         });
@@ -248,7 +249,8 @@ void b_vcycle(cps_batch* B, BatchGroup& G)
         if (!G.gs[l].count) continue;
         // point red-black post-smoothing starts with the black pass: only
         // the red cells need the correction (as vcycle())
-        if (!G.plane && G.ncol == 2) blaunch(B, G.xfer[l], kb_prolong<float, 1>, l);
+        if (G.plane) blaunch(B, G.xfer[l], kb_prolong<float, 2>, l);
+        else if (G.ncol == 2) blaunch(B, G.xfer[l], kb_prolong<float, 1>, l);
         else blaunch(B, G.xfer[l], kb_prolong<float, 0>, l);
         b_smooth(B, G, l, true, false);
     }

@@ -546,13 +546,14 @@ long long smooth(cps_handle* h, int l, const T* b, T* x, int sweeps, bool revers
 }
 
 // r = b - A x; partial sums of r^2 into h->partial when want_norm.
-// red: x has just been smoothed red-black with the black pass last, and on a
+// red 1: x has just been smoothed red-black with the black pass last, and on a
 // row-pair level only r's red cells are formed (the black ones are zero, and
-// are left stale: only restrict_to(red) reads this r).  Returns the number
-// of partial sums written.
+// are left stale: only restrict_to(red) reads this r).  red 2: x has been
+// smoothed by planes, and only the even rows are formed.  Returns the number of
+// partial sums written.
 template <typename T>
 long long residual(cps_handle* h, int l, const T* b, const T* x, T* r, bool want_norm,
-                   bool red = false)
+                   int red = 0)
 {
     const Level<T> L = view<T>(h, l);
     const int bpa = (int)nblk(L.g.rowlen);
@@ -563,16 +564,17 @@ long long residual(cps_handle* h, int l, const T* b, const T* x, T* r, bool want
         if (row_pairs(L.g)) {
             if (l == 0)
                 k_residual_march2<T, 0><<<ms.grid, kBlock, 0, h->stream>>>(
-                    L.g, L.G, L.gk, ms.bpa, ms.ch, b, x, r, part, red ? 1 : 0);
+                    L.g, L.G, L.gk, ms.bpa, ms.ch, b, x, r, part, red);
             else
                 k_residual_march2<T, 1><<<ms.grid, kBlock, 0, h->stream>>>(
-                    L.g, L.G, L.gk, ms.bpa, ms.ch, b, x, r, part, red ? 1 : 0);
+                    L.g, L.G, L.gk, ms.bpa, ms.ch, b, x, r, part, red);
             LAUNCH_CHECK();
             return ms.grid;
         }
         auto launch = [&](auto U, auto T_) {
             k_residual_march<T, decltype(U)::value, decltype(T_)::value>
-                <<<ms.grid, kBlock, 0, h->stream>>>(L.g, L.G, L.gk, ms.bpa, ms.ch, b, x, r, part);
+                <<<ms.grid, kBlock, 0, h->stream>>>(L.g, L.G, L.gk, ms.bpa, ms.ch, b, x, r, part,
+                                                    red);
         };
         const bool u = L.g.nh % 64 == 0;
         if (l == 0) u ? launch(BA<true>{}, IM<0>{}) : launch(BA<false>{}, IM<0>{});
@@ -582,7 +584,7 @@ long long residual(cps_handle* h, int l, const T* b, const T* x, T* r, bool want
     }
     dispatch4(h->mode, h->axi, L.g.nh % 64 == 0, l == 0 ? 0 : 1, [&](auto M, auto A, auto U, auto T_) {
         k_residual<T, decltype(M)::value, decltype(A)::value, decltype(U)::value, decltype(T_)::value>
-            <<<grid_of(L.g.nr, bpa), kBlock, 0, h->stream>>>(L.g, L.G, L.gk, bpa, b, x, r, part);
+            <<<grid_of(L.g.nr, bpa), kBlock, 0, h->stream>>>(L.g, L.G, L.gk, bpa, b, x, r, part, red);
     });
     LAUNCH_CHECK();
     return grid_of(L.g.nr, bpa);
@@ -665,16 +667,19 @@ void dot(cps_handle* h, long long n, const T* u, const U* v, int slot, int ops =
     reduce(h, vgrid(n), slot, 0, ops);
 }
 
-// red: r is residual(red)'s output, of which only the red cells are read.
+// red: r is residual(red)'s output, of which only the red cells (2: the even
+// rows) are read.
 template <typename T>
-void restrict_to(cps_handle* h, int l, const T* r, T* bc, bool red = false)
+void restrict_to(cps_handle* h, int l, const T* r, T* bc, int red = 0)
 {
     const Geo& f = h->lv[l].geo;
     const Geo& c = h->lv[l + 1].geo;
     const MarchShape ms = restrict_shape(c);
     ProfScope ps(h, CPS_KERNEL_RESTRICT, l);
     if (!restrict_rows(c))
-        k_restrict<T><<<ms.grid, kBlock, 0, h->stream>>>(f, c, ms.bpa, ms.ch, r, bc, red ? 1 : 0);
+        k_restrict<T><<<ms.grid, kBlock, 0, h->stream>>>(f, c, ms.bpa, ms.ch, r, bc, red);
+    else if (red == 2)
+        k_restrict_rows<T, 2><<<ms.grid, kBlock, 0, h->stream>>>(f, c, ms.bpa, ms.ch, r, bc);
     else if (red)
         k_restrict_rows<T, 1><<<ms.grid, kBlock, 0, h->stream>>>(f, c, ms.bpa, ms.ch, r, bc);
     else
@@ -710,16 +715,18 @@ bool red_residual(const cps_handle* h, int l)
     return h->opts.smoother == 0 && marching(h) && h->ncol == 2 && row_pairs(h->lv[l].geo);
 }
 
-// red: only level l's red cells are corrected (a red-black post-smoothing
-// follows, whose first pass overwrites every black cell unread)
+// red 1: only level l's red cells are corrected (a red-black post-smoothing
+// follows, whose first pass overwrites every black cell unread); 2: its even
+// rows (a plane one, whose first half-sweep overwrites the odd rows)
 template <typename T>
-void prolong_add(cps_handle* h, int l, const T* e, T* x, bool red = false)
+void prolong_add(cps_handle* h, int l, const T* e, T* x, int red = 0)
 {
     const Geo& f = h->lv[l].geo;
     const Geo& c = h->lv[l + 1].geo;
     const MarchShape ms = march_shape(c);
     ProfScope ps(h, CPS_KERNEL_PROLONG, l);
-    if (red) k_prolong<T, 1><<<ms.grid, kBlock, 0, h->stream>>>(f, c, ms.bpa, ms.ch, e, x);
+    if (red == 2) k_prolong<T, 2><<<ms.grid, kBlock, 0, h->stream>>>(f, c, ms.bpa, ms.ch, e, x);
+    else if (red) k_prolong<T, 1><<<ms.grid, kBlock, 0, h->stream>>>(f, c, ms.bpa, ms.ch, e, x);
     else k_prolong<T, 0><<<ms.grid, kBlock, 0, h->stream>>>(f, c, ms.bpa, ms.ch, e, x);
     LAUNCH_CHECK();
 }
@@ -817,8 +824,8 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
         // point red-black smoothing ends on the black pass: on row-pair
         // levels only the red residual is formed and restricted (in one pass
         // where the level's shape allows it)
-        const bool red = red_residual(h, l);
-        if (red && resrestrict_segs(h->lv[l].geo, h->lv[l + 1].geo) > 0) {
+        const int red = h->opts.smoother == 1 ? 2 : (red_residual(h, l) ? 1 : 0);
+        if (red == 1 && resrestrict_segs(h->lv[l].geo, h->lv[l + 1].geo) > 0) {
             resrestrict<T>(h, l, b, x, bl<T>(h, l + 1));
             continue;
         }
@@ -849,7 +856,7 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
         }
         // point red-black post-smoothing starts with the black pass: only
         // the red cells need the correction
-        prolong_add<T>(h, l, e, x, h->opts.smoother == 0 && h->ncol == 2);
+        prolong_add<T>(h, l, e, x, h->opts.smoother == 1 ? 2 : (h->ncol == 2 ? 1 : 0));
         const bool d = dot && l == 0 && marching(h);
         parts = smooth<T>(h, l, b, x, 2, true, false, d ? h->partial.p : nullptr);
     }

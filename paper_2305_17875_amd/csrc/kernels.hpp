@@ -398,11 +398,12 @@ template <typename T, int MODE, bool AXI, bool UROW, int LTAG>
 __device__ __forceinline__ void d_residual(Blk bk, Geo g, const T* __restrict__ G, long long gk,
                                                      int bpa, const T* __restrict__ bv,
                                                      const T* __restrict__ x, T* __restrict__ r,
-                                                     double* __restrict__ partial)
+                                                     double* __restrict__ partial, int red = 0)
 {
     double acc = 0.0;
     for_units(bk, g.rowlen, bpa, (long long)g.nr * bpa, [&](int a, int m) {
         const int b = row_of<UROW>(m, g.nh), j = m - b * g.nh;
+        if (red == 2 && (b & 1)) return;
         const long long i0 = (long long)a * g.rowlen + m;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -423,9 +424,9 @@ template <typename T, int MODE, bool AXI, bool UROW, int LTAG>
 __global__ void __launch_bounds__(kBlock) k_residual(Geo g, const T* __restrict__ G, long long gk,
                                                      int bpa, const T* __restrict__ bv,
                                                      const T* __restrict__ x, T* __restrict__ r,
-                                                     double* __restrict__ partial)
+                                                     double* __restrict__ partial, int red)
 {
-    d_residual<T, MODE, AXI, UROW, LTAG>(self_blk(), g, G, gk, bpa, bv, x, r, partial);
+    d_residual<T, MODE, AXI, UROW, LTAG>(self_blk(), g, G, gk, bpa, bv, x, r, partial, red);
 }
 
 // One Gauss-Seidel pass over the cells of one colour, in place:
@@ -694,18 +695,22 @@ __device__ __forceinline__ void march_start(const Geo& g, const X& x, const Marc
     vm = x[g.P + bm];
 }
 
-// r = b - A x (and partial sums of r^2), marching.
+// r = b - A x (and partial sums of r^2), marching.  red == 2: on the even
+// theta rows only (after plane smoothing whose last half-sweep was that of the
+// odd rows: their equations hold as they stand, and the restriction takes their
+// residual as zero without reading it); the same in d_residual.
 template <typename T, bool UROW, int LTAG>
 __device__ __forceinline__ void d_residual_march(Blk bk, Geo g, const T* __restrict__ G,
                                                            long long gk, int bpa, int ch,
                                                            const T* __restrict__ bv,
                                                            const T* __restrict__ x,
                                                            T* __restrict__ r,
-                                                           double* __restrict__ partial)
+                                                           double* __restrict__ partial,
+                                                           int red = 0)
 {
     March p;
     double acc = 0.0;
-    if (march_pos<UROW>(bk, g, bpa, ch, p)) {
+    if (march_pos<UROW>(bk, g, bpa, ch, p) && !(red == 2 && (p.b & 1))) {
         T um, u0, vm, v0;
         march_start<T>(g, x, p, um, u0, vm, v0);
         for (int a = p.a0; a < p.a1; a += kAhead2) {
@@ -745,9 +750,9 @@ __global__ void __launch_bounds__(kBlock) k_residual_march(Geo g, const T* __res
                                                            const T* __restrict__ bv,
                                                            const T* __restrict__ x,
                                                            T* __restrict__ r,
-                                                           double* __restrict__ partial)
+                                                           double* __restrict__ partial, int red)
 {
-    d_residual_march<T, UROW, LTAG>(self_blk(), g, G, gk, bpa, ch, bv, x, r, partial);
+    d_residual_march<T, UROW, LTAG>(self_blk(), g, G, gk, bpa, ch, bv, x, r, partial, red);
 }
 
 // y = A x (and partial sums of y . dotv), marching.
@@ -1253,13 +1258,14 @@ __device__ __forceinline__ void march2_start(const Geo& g, const X& x, const Mar
 }
 
 // r = b - A x (and partial sums of r^2) over row pairs.
-// red != 0: the residual after a red-black smoothing whose last pass was
+// red == 1: the residual after a red-black smoothing whose last pass was
 // the black one (colour 1).  Each black cell's update made its own equation
 // hold with its red neighbours as they stand, and none has changed since, so
 // its residual is zero (in exact arithmetic; rounding leaves ~1e-16 of b).
 // Only the red cells (colour 0: plane (a + b) mod 2 of row b at plane a) are
 // formed: b is read and r written there only, and r's black entries are
 // left as they are -- the restriction (red != 0) never reads them.  No norm.
+// red == 2: the even rows only, as d_residual_march.
 template <typename T, int LTAG, int AHEAD = 1>
 __device__ __forceinline__ void d_residual_march2(Blk bk, Geo g, const T* __restrict__ G,
                                                             long long gk, int bpa, int ch,
@@ -1280,11 +1286,13 @@ __device__ __forceinline__ void d_residual_march2(Blk bk, Geo g, const T* __rest
             T bb[AHEAD][4];
             // the red cells of the pair at plane a: (u0, v1) for even a,
             // (v0, u1) for odd a (row b0 is even)
-            auto is_red = [&](int k, int aa) { return (((k == 1 || k == 2) ? 1 : 0) ^ (aa & 1)) == 0; };
+            auto is_red = [&](int k, int aa) {
+                return red == 2 ? k < 2 : (((k == 1 || k == 2) ? 1 : 0) ^ (aa & 1)) == 0;
+            };
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u)
                 if (a + u < p.a1) {
-                    march2_load<T>(g, Plain<T>{x}, p, a + u, nb[u]);
+                    march2_load<T>(g, Plain<T>{x}, p, a + u, nb[u], true, red != 2);
                     const long long base = (long long)(a + u) * g.rowlen + p.r0;
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
@@ -1584,7 +1592,8 @@ __device__ __forceinline__ bool coarse_col(Blk bk, const Geo& c, int bpa, int ch
 // bc = R r (full weighting; interior rows sum to 8).  red != 0: r is the
 // red-only residual of d_residual_march2 (zero on the black cells, whose
 // entries hold stale values): of each fine row only its red parity plane,
-// (plane + row) mod 2, is read, the other taken as zero.
+// (plane + row) mod 2, is read, the other taken as zero.  red == 2: the odd
+// rows are taken as zero and not read.
 template <typename T>
 __device__ __forceinline__ void d_restrict(Blk bk, Geo f, Geo c, int bpa, int ch,
                                                      const T* __restrict__ r,
@@ -1608,6 +1617,11 @@ __device__ __forceinline__ void d_restrict(Blk bk, Geo f, Geo c, int bpa, int ch
     const int lane = (int)(threadIdx.x & 63);
     const bool lo_lane = lane > 0 && p.jc > 0;
     const bool hi_lane = lane < 63 && p.jc < c.nh - 1;
+    // parity plane s of a fine row holds values to read (red: the row's red
+    // cells are in plane (ac + row) mod 2)
+    auto reads = [&](int ac, int row, int s) {
+        return red == 0 || (red == 2 ? (row & 1) == 0 : ((ac + row) & 1) == s);
+    };
     // theta-phi restriction of fine plane a for K = 2jc (s0) and 2jc+1 (s1)
     auto plane = [&](int a, T& s0, T& s1) {
         const int ac = clampi(a, f.nr - 1);
@@ -1618,18 +1632,17 @@ __device__ __forceinline__ void d_restrict(Blk bk, Geo f, Geo c, int bpa, int ch
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const T* rr = ra + rowo[q];
-            // red: the row's red cells are in plane (ac + row) mod 2
-            const int sp = (ac + (int)(rowo[q] / f.nh)) & 1;
-            e[q] = !red || sp == 0 ? *reinterpret_cast<const Vec2<T>*>(rr + cv) : zero2;
-            o[q] = !red || sp == 1 ? *reinterpret_cast<const Vec2<T>*>(rr + f.P + cv) : zero2;
+            const int row = (int)(rowo[q] / f.nh);
+            e[q] = reads(ac, row, 0) ? *reinterpret_cast<const Vec2<T>*>(rr + cv) : zero2;
+            o[q] = reads(ac, row, 1) ? *reinterpret_cast<const Vec2<T>*>(rr + f.P + cv) : zero2;
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int sp = (ac + (int)(rowo[q] / f.nh)) & 1;
+            const int row = (int)(rowo[q] / f.nh);
             v0[q] = __shfl(o[q].y, lane - 1);
             v5[q] = __shfl(e[q].x, lane + 1);
-            if (!lo_lane) v0[q] = !red || sp == 1 ? ra[rowo[q] + cm] : T(0);
-            if (!hi_lane) v5[q] = !red || sp == 0 ? ra[rowo[q] + cp] : T(0);
+            if (!lo_lane) v0[q] = reads(ac, row, 1) ? ra[rowo[q] + cm] : T(0);
+            if (!hi_lane) v5[q] = reads(ac, row, 0) ? ra[rowo[q] + cp] : T(0);
         }
         s0 = T(0);
         s1 = T(0);
@@ -1672,9 +1685,10 @@ __device__ __forceinline__ void d_restrict(Blk bk, Geo f, Geo c, int bpa, int ch
 // loads of a plane are issued as soon as its buffer is consumed, two planes
 // before it is restricted.
 //
-// RED (d_residual_march2's red residual): of each fine row only its red
+// RED 1 (d_residual_march2's red residual): of each fine row only its red
 // parity plane, (plane + row) mod 2, is read -- one 2-vector and one outer
-// phi value per row -- and the black values enter as zeros.
+// phi value per row -- and the black values enter as zeros.  RED 2: the odd
+// rows enter as zeros.
 template <typename T>
 struct RestrictLds {
     Vec2<T> v[2][4][2][64];
@@ -1734,7 +1748,11 @@ __device__ __forceinline__ void d_restrict2(Blk bk, Geo f, Geo c, int bpa, int c
         for (int k = 0; k < 3; ++k) {
             if (k == 2 && !outer) continue;
             const T* rr = ra + (long long)rows[k] * f.nh;
-            if constexpr (RED) {
+            if (RED == 2 && (rows[k] & 1)) {
+                q[k] = Raw{};
+                continue;
+            }
+            if constexpr (RED == 1) {
                 const int sp = (ac + rows[k]) & 1;
                 q[k].v = *reinterpret_cast<const Vec2<T>*>(rr + (sp ? f.P : 0) + cv);
                 q[k].edge = (sp ? !lo_lane : !hi_lane) ? rr[sp ? cm : cp] : T(0);
@@ -1749,7 +1767,7 @@ __device__ __forceinline__ void d_restrict2(Blk bk, Geo f, Geo c, int bpa, int c
     // phi restriction of one row's raw values, for K = 2jc (q0) and 2jc + 1
     // (q1); fine phi 4jc - 1 .. 4jc + 4 are v0 .. v5
     auto phi = [&](int ac, int row, const Raw& q, T& q0, T& q1) {
-        if constexpr (RED) {
+        if constexpr (RED == 1) {
             if (((ac + row) & 1) == 0) { // red in plane 0: v1, v3, v5
                 T v5 = __shfl(q.v.x, lane + 1);
                 if (!hi_lane) v5 = q.edge;
@@ -1839,7 +1857,8 @@ __device__ __forceinline__ void d_restrict_any(Blk bk, Geo f, Geo c, int bpa, in
                                                RestrictLds<T>& sh, int red)
 {
     if (!restrict_rows(c)) d_restrict<T>(bk, f, c, bpa, ch, r, bc, red);
-    else if (red) d_restrict2<T, 1>(bk, f, c, bpa, ch, r, bc, sh);
+    else if (red == 1) d_restrict2<T, 1>(bk, f, c, bpa, ch, r, bc, sh);
+    else if (red == 2) d_restrict2<T, 2>(bk, f, c, bpa, ch, r, bc, sh);
     else d_restrict2<T, 0>(bk, f, c, bpa, ch, r, bc, sh);
 }
 
@@ -2075,10 +2094,11 @@ __global__ void __launch_bounds__(64 * rr_waves(SEGS))
 
 // x += P e (trilinear); the thread writes fine rows 2J, 2J+1 and fine phi
 // 4jc .. 4jc+3 on the two fine planes of every coarse plane of its chunk.
-// RED: only the red cells (colour 0) are corrected -- read and written.  A
+// RED 1: only the red cells (colour 0) are corrected -- read and written.  A
 // red-black post-smoothing starts with the black pass, which reads only red
 // values and overwrites every black cell, so the black cells' correction is
-// never read; it is not made (half the fine level's bytes).
+// never read; it is not made (half the fine level's bytes).  RED 2: only the even
+// theta rows (a plane post-smoothing starts with the odd ones, unread).
 template <typename T, int RED = 0>
 __device__ __forceinline__ void d_prolong(Blk bk, Geo f, Geo c, int bpa, int ch,
                                                     const T* __restrict__ e,
@@ -2126,6 +2146,8 @@ __device__ __forceinline__ void d_prolong(Blk bk, Geo f, Geo c, int bpa, int ch,
             fo[rr][sp] = (long long)sp * f.P + (long long)(2 * p.J + rr) * f.nh + 2 * p.jc;
     // the red cells of fine row 2J + rr sit in plane (a + rr) mod 2 at fine
     // plane a: sp == rr on the even plane 2I, sp != rr on the odd one
+    auto on0 = [](int rr, int sp) { return RED == 0 || (RED == 2 ? rr == 0 : sp == rr); };
+    auto on1 = [](int rr, int sp) { return RED == 0 || (RED == 2 ? rr == 0 : sp != rr); };
     for (int I = p.I0; I < p.I1; ++I) {
         plane(I + 1, tp);
         T* x0 = x + (long long)(2 * I) * f.rowlen;
@@ -2135,19 +2157,19 @@ __device__ __forceinline__ void d_prolong(Blk bk, Geo f, Geo c, int bpa, int ch,
         for (int rr = 0; rr < 2; ++rr)
 #pragma unroll
             for (int sp = 0; sp < 2; ++sp) {
-                if (!RED || sp == rr) y0[rr][sp] = *reinterpret_cast<const Vec2<T>*>(x0 + fo[rr][sp]);
-                if (!RED || sp != rr) y1[rr][sp] = *reinterpret_cast<const Vec2<T>*>(x1 + fo[rr][sp]);
+                if (on0(rr, sp)) y0[rr][sp] = *reinterpret_cast<const Vec2<T>*>(x0 + fo[rr][sp]);
+                if (on1(rr, sp)) y1[rr][sp] = *reinterpret_cast<const Vec2<T>*>(x1 + fo[rr][sp]);
             }
 #pragma unroll
         for (int rr = 0; rr < 2; ++rr)
 #pragma unroll
             for (int sp = 0; sp < 2; ++sp) {
-                if (!RED || sp == rr) {
+                if (on0(rr, sp)) {
                     y0[rr][sp].x += w0 * t0[rr][sp] + w1 * tm[rr][sp];
                     y0[rr][sp].y += w0 * t0[rr][sp + 2] + w1 * tm[rr][sp + 2];
                     *reinterpret_cast<Vec2<T>*>(x0 + fo[rr][sp]) = y0[rr][sp];
                 }
-                if (!RED || sp != rr) {
+                if (on1(rr, sp)) {
                     y1[rr][sp].x += w0 * t0[rr][sp] + w1 * tp[rr][sp];
                     y1[rr][sp].y += w0 * t0[rr][sp + 2] + w1 * tp[rr][sp + 2];
                     *reinterpret_cast<Vec2<T>*>(x1 + fo[rr][sp]) = y1[rr][sp];
@@ -2966,8 +2988,8 @@ __global__ void __launch_bounds__(kBlock) kb_gs(const BItem* __restrict__ items,
 }
 
 // r = b - A x on a level (no norm), marching (7-point, phi-invariant) or generic
-// red: the group smooths red-black (not by planes): on row-pair levels the
-// red-only residual, as the single solve forms it
+// red 1: the group smooths red-black: on row-pair levels the red-only residual,
+// as the single solve forms it; 2: by planes, the even rows only
 template <typename T, int MODE, bool AXI>
 __global__ void __launch_bounds__(kBlock) kb_residual(const BItem* __restrict__ items,
                                                       const int* __restrict__ active,
@@ -2980,12 +3002,12 @@ __global__ void __launch_bounds__(kBlock) kb_residual(const BItem* __restrict__ 
     if constexpr (MODE == MODE_ORTHO && AXI) {
         const MarchShape ms = stencil_shape(d.g);
         if (row_pairs(d.g)) d_residual_march2<T, 1>(bk, d.g, d.G, d.gk, ms.bpa, ms.ch, d.b, d.x, d.r, nullptr, red);
-        else if (u) d_residual_march<T, true, 1>(bk, d.g, d.G, d.gk, ms.bpa, ms.ch, d.b, d.x, d.r, nullptr);
-        else d_residual_march<T, false, 1>(bk, d.g, d.G, d.gk, ms.bpa, ms.ch, d.b, d.x, d.r, nullptr);
+        else if (u) d_residual_march<T, true, 1>(bk, d.g, d.G, d.gk, ms.bpa, ms.ch, d.b, d.x, d.r, nullptr, red);
+        else d_residual_march<T, false, 1>(bk, d.g, d.G, d.gk, ms.bpa, ms.ch, d.b, d.x, d.r, nullptr, red);
     } else {
         const int bpa = cdiv(d.g.rowlen, kBlock);
-        if (u) d_residual<T, MODE, AXI, true, 1>(bk, d.g, d.G, d.gk, bpa, d.b, d.x, d.r, nullptr);
-        else d_residual<T, MODE, AXI, false, 1>(bk, d.g, d.G, d.gk, bpa, d.b, d.x, d.r, nullptr);
+        if (u) d_residual<T, MODE, AXI, true, 1>(bk, d.g, d.G, d.gk, bpa, d.b, d.x, d.r, nullptr, red);
+        else d_residual<T, MODE, AXI, false, 1>(bk, d.g, d.G, d.gk, bpa, d.b, d.x, d.r, nullptr, red);
     }
 }
 
@@ -3000,7 +3022,7 @@ __global__ void __launch_bounds__(kBlock) kb_restrict(const BItem* __restrict__ 
     const PDesc<T>& P = pd[it.prob];
     const MarchShape ms = march_shape(P.lv[level + 1].g);
     d_restrict_any<T>(bk, P.lv[level].g, P.lv[level + 1].g, ms.bpa, ms.ch, P.lv[level].r,
-                      P.lv[level + 1].b, sh, red && row_pairs(P.lv[level].g));
+                      P.lv[level + 1].b, sh, red == 1 && !row_pairs(P.lv[level].g) ? 0 : red);
 }
 
 // the fused red residual and restriction of one problem's level (SEGS as

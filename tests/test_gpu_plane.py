@@ -272,3 +272,30 @@ def test_vcycle_starts_coarse_levels_from_zero(shape, map_):
             assert relmax(x, want) < 1e-11, relmax(x, want)
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("shape", [(8, 16, 512), (8, 12, 256), (6, 10, 64)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("map_", [MAP_IDENTITY, MAP_OBLATE], ids=["box", "oblate"])
+def test_transfers_of_the_even_rows(shape, map_):
+    """After pre-smoothing the odd rows' equations hold, and post-smoothing
+    overwrites those rows first: residual, restriction and correction take the
+    even ones only.  The forms by ring and rows (row pairs with the row-wise and
+    the general restriction, neither), a V-cycle against the oracle's, which
+    takes all rows: to 1e-11 relative."""
+    g = Shell(*shape, map=map_, flattening=0.1 if map_ == MAP_OBLATE else 0.0)
+    s = cps.Solver(g, precision=0, accel=0, smoother=1, n_levels=2 if shape[2] == 64 else 3)
+    try:
+        mg = O.Multigrid(g, n_levels=2 if shape[2] == 64 else 3)
+        rng = np.random.default_rng(7)
+        b = rng.standard_normal(shape)
+        b -= b.mean()
+        x = rng.standard_normal(shape) * 0.1
+        want = plane.PlaneMultigrid(mg, nu=2).vcycle(b, x)
+        xd = dev(x).flatten()
+        cps.cps_debug_vcycle(s.h, dev(b).flatten(), xd)
+        err = relmax(host(xd).reshape(shape), want)
+        log("even rows", map_, shape, err)
+        assert err < 1e-11, err
+    finally:
+        s.close()
