@@ -431,7 +431,7 @@ __global__ void __launch_bounds__(kBlock) k_line_fft(int nr, int nt, int np, dou
 #pragma unroll
             for (int u = 0; u < kLdBatch; ++u) {
                 const int j = j0 + u * pl.tpr;
-                if (j < nh) A[j] = z[u];
+                if (j < nh) A[sw<double, NMAX>(j)] = z[u];
             }
         }
     __syncthreads(); // twiddles of the block (the ring's values are wave-local)
@@ -470,17 +470,17 @@ __global__ void __launch_bounds__(kBlock) k_line_fft(int nr, int nt, int np, dou
     };
     for (int m = tr; m <= nh / 2; m += pl.tpr) {
         const int k = nh - m;
-        const Vec2<double> Zm = A[m], Zk = A[k == nh ? 0 : k];
+        const Vec2<double> Zm = A[sw<double, NMAX>(m)], Zk = A[sw<double, NMAX>(k == nh ? 0 : k)];
         const Vec2<double> Ym = real_mode(Zm, conjv(Zk), m);
         const Vec2<double> Yk = real_mode(Zk, conjv(Zm), k);
-        A[m] = half_seq(Ym, conjv(Yk), m);
-        if (k != m && k < nh) A[k] = half_seq(Yk, conjv(Ym), k);
+        A[sw<double, NMAX>(m)] = half_seq(Ym, conjv(Yk), m);
+        if (k != m && k < nh) A[sw<double, NMAX>(k)] = half_seq(Yk, conjv(Ym), k);
     }
     wave_sync();
     wave_fft<double, NMAX>(A, nh, tr, pl.tpr, twS, true);
     const double sc = 1.0 / nh;
     for (int j = tr; j < nh; j += pl.tpr) {
-        Vec2<double> v = A[j];
+        Vec2<double> v = A[sw<double, NMAX>(j)];
         v.x *= sc;
         v.y *= sc;
         *reinterpret_cast<Vec2<double>*>(psi + base + 2 * j) = v;
