@@ -176,13 +176,15 @@ struct PlaneLaunch {
 };
 
 // rows of parity k; lanes per ring (a power of two <= 64, so a ring never
-// straddles wavefronts), rings per block (<= 256 lanes, <= kPlaneLds values;
+// straddles wavefronts; four values of a ring a lane, so that a radix-4 stage
+// keeps every lane busy: against two, a batch of 16 with rings of 128 to 256
+// cells 34.1 -> 32.9 ms), rings per block (<= 256 lanes, <= kPlaneLds values;
 // rb > 0 asks for at most that many: the autotuner's choice)
 __host__ __device__ inline PlaneLaunch plane_launch(const Geo& g, int parity, int rb = 0)
 {
     PlaneLaunch p;
     p.rows = (g.nt - parity + 1) / 2;
-    p.tpr = g.nh / 2 < 64 ? g.nh / 2 : 64;
+    p.tpr = g.nh < 8 ? 1 : (g.nh / 4 < 64 ? g.nh / 4 : 64);
     p.rb = kBlock / p.tpr;
     if (p.rb * g.nh > kPlaneLds) p.rb = kPlaneLds / g.nh;
     if (rb > 0 && rb < p.rb) p.rb = rb;
