@@ -1439,7 +1439,7 @@ void build(cps_handle* h)
     if (h->opts.smoother == 1) setup_plane(h);
     // small levels of the point smoother run the tile path (not the
     // coarsest: it is solved directly; the finest only when the cycle starts
-    // from zero, and then its dot products come from a separate reduction)
+    // from zero)
     for (int l = 0; l + 1 < h->L; ++l) {
         LevelMem& m = h->lv[l];
         const bool point7 = marching(h) && h->ncol == 2 && h->opts.smoother == 0;

@@ -27,6 +27,8 @@
 //    and the pivots cross memory once and the serial chain is 16 steps long
 //    instead of n_r;
 //  - k_plane_inv: the inverse transform back into the rows.
+// Rows whose plane is small take one launch, k_plane_row, a block per row.  The
+// first half-sweep from a zero iterate does not read it.
 // Spectra and pivots are laid out [a][row][mode], so the r-line solves read
 // and write consecutive modes across a wavefront.  The modes 0 and n_phi / 2
 // of a real ring are real: they share slot 0 (real and imaginary part), so

@@ -178,8 +178,8 @@ def vcycle_traffic(a, fe, wr, sf, sw):
     print(json.dumps(out, indent=1))
 
 
-STEP_KERNELS = ("k_divergence", "k_divergence2", "k_correct", "k_line_factor", "k_line_open",
-                "k_line_fft", "k_line_periodic")
+STEP_KERNELS = ("k_divergence", "k_divergence2", "k_correct", "k_line_factor", "k_line_chunk",
+                "k_line_open", "k_line_fft", "k_line_periodic")
 
 
 def step_summary(a, dur, fe, wr, sf, sw):
