@@ -417,11 +417,12 @@ def lines_form(cps, torch, inputs, g, steps, warmup):
     """The implicit line solves of the ADI steps (cps_line_solve) along each
     direction on the paper-scale shell, coef 1e-4, value 0 on the low wall
     and no flux on the high wall.  Timed with events on the solve stream;
-    rates against the design's bytes per cell: open r- and theta-lines read
-    the right-hand side and write psi on the way down, read and write psi on
-    the way up (4 words); periodic phi-lines with a power-of-two ring are
-    solved by one transform per ring in LDS (read once, written once: 2
-    words), other rings by the split with a closing row (12 words)."""
+    rates against the design's bytes per cell: open r- and theta-lines of up
+    to 256 cells are read and written once (2 words), longer ones read the
+    right-hand side and write psi on the way down, read and write psi on the
+    way up (4 words); periodic phi-lines with a power-of-two ring are solved by
+    one transform per ring in LDS (read once, written once: 2 words), other
+    rings by the split with a closing row (12 words)."""
     n = g.cells
     rhs = torch.from_numpy(inputs.smoothed_noise(g.shape, 50)).cuda().flatten()
     psi = torch.empty_like(rhs)
@@ -431,7 +432,9 @@ def lines_form(cps, torch, inputs, g, steps, warmup):
     bc = (1, 0.0, 0, 0.0)
     nh = g.n_phi // 2
     phi_words = 2 if nh >= 2 and nh & (nh - 1) == 0 and nh <= 1024 else 12
-    for d, name, words in ((0, "r", 4), (1, "theta", 4), (2, "phi_periodic", phi_words)):
+    r_words, t_words = (2 if m <= 256 else 4 for m in (g.n_r, g.n_theta))
+    for d, name, words in ((0, "r", r_words), (1, "theta", t_words),
+                           (2, "phi_periodic", phi_words)):
         for _ in range(warmup):
             s.line_solve(d, 1e-4, rhs, bc, out=psi)
         ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
@@ -818,7 +821,7 @@ def serve_form(cps, inputs, duration, rate, slots, budget_gib, comparator_s, smo
 
 def vcycle_traffic():
     """Counter bytes of one FP64 V-cycle (profiles/), if they were taken on
-    the current kernel sources (kernels.hpp and tile.hpp)."""
+    the current kernel sources (kernels.hpp, tile.hpp and march.hpp)."""
     try:
         d = json.load(open(VCYCLE_TRAFFIC_FILE))
     except (OSError, ValueError):
@@ -827,6 +830,8 @@ def vcycle_traffic():
     for path in (KERNEL_SRC, TILE_SRC):
         h.update(open(path, "rb").read())
     if d.get("source_sha256_16") != h.hexdigest()[:16]:
+        return None
+    if d.get("march_sha256_16", kernel_hash(MARCH_SRC)) != kernel_hash(MARCH_SRC):
         return None
     return d.get("bytes_per_cycle")
 

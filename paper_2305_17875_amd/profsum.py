@@ -13,7 +13,7 @@ Counter values (KiB per dispatch) are scaled by what the same counter reads
 on the library's plain copy kernel (k_copy) over 192*256*512 doubles
 (201,326,592 bytes read and written; every solve copies its right-hand side
 with it), which turns them into bytes.  The traffic JSON records
-the finest-level Gauss-Seidel kernel's bytes per launch together with a hash
+the finest-level post-smoothing kernel's bytes per launch together with a hash
 of the kernel source, so bench.py can tell whether it is still current.  The
 plane outputs do the same for the three kernels of one zebra half-sweep of
 the plane smoother on the finest level (largest grid of each), FP64 and
@@ -32,9 +32,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SRC = os.path.join(HERE, "csrc", "kernels.hpp")
 TILE_SRC = os.path.join(HERE, "csrc", "tile.hpp")
 PLANE_SRC = os.path.join(HERE, "csrc", "plane.hpp")
+MARCH_SRC = os.path.join(HERE, "csrc", "march.hpp")
 PLANE_KERNELS = ("k_plane_fwd", "k_plane_tri", "k_plane_inv")
 COPY_BYTES = 192 * 256 * 512 * 8
-GS_FINEST = "k_gs_march2<double, 0, 0>"
+UP_FINEST = "k_vpost_march<double>"
 
 
 def short(name: str) -> str:
@@ -65,6 +66,12 @@ def mean(v):
     return sum(v) / len(v)
 
 
+def finest(v):
+    """The finest level's launches of a kernel whose levels share one grid: those
+    above half of the largest (a coarser level has an eighth of the cells)."""
+    return [x for x in v if x > 0.5 * max(v)]
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--kt", required=True)
@@ -79,7 +86,7 @@ def main():
     ap.add_argument("--step-md", help="projection step and ADI line-solve kernels")
     ap.add_argument("--vcycle-traffic", help="counter bytes of one FP64 V-cycle (JSON)")
     a = ap.parse_args()
-    kh = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()[:16]
+    kh = hashlib.sha256(open(MARCH_SRC, "rb").read()).hexdigest()[:16]
     dur = durations(a.kt)
     fe = counters(a.fetch)
     wr = counters(a.write)
@@ -92,7 +99,7 @@ def main():
     lines = [f"# rocprofv3 summary: bench.py (spherical shell 192x256x512, FP64 PCG-multigrid)",
              "", "Commands (run from the repository root on one MI355X):", "", "```",
              a.cmd, "```", "",
-             f"kernel source sha256[:16] = `{kh}`", "",
+             f"march.hpp sha256[:16] = `{kh}`", "",
              "## Kernel durations (--kernel-trace --stats)", "",
              "| kernel | grid (threads) | launches | avg us | total ms |", "|---|---|---|---|---|"]
     for (n, g), v in sorted(dur.items(), key=lambda kv: -sum(kv[1]))[:a.top]:
@@ -102,26 +109,22 @@ def main():
               f"and {copy_w:.1f} KiB written, so fetch x{sf:.3f}, write x{sw:.3f}.", "",
               "| kernel | grid (threads) | fetch MB | write MB |", "|---|---|---|---|"]
     keys = sorted({(n, g) for (n, g, cn) in fe}, key=lambda k: -mean(fe[(k[0], k[1], 'FETCH_SIZE')]))
-    gs = None
     for n, g in keys[:a.top]:
         f = mean(fe[(n, g, "FETCH_SIZE")]) * 1024 * sf
         w = mean(wr.get((n, g, "WRITE_SIZE"), [0.0])) * 1024 * sw
         lines.append(f"| `{n}` | {g} | {f / 1e6:.1f} | {w / 1e6:.1f} |")
-        if n.startswith(GS_FINEST):
-            gs = (f, w, g)
-    if gs is None:
-        for (n, g, cn), v in fe.items():
-            if n.startswith(GS_FINEST):
-                gs = (mean(v) * 1024 * sf, mean(wr[(n, g, "WRITE_SIZE")]) * 1024 * sw, g)
-    gsd = [v for (n, g), v in dur.items() if n.startswith(GS_FINEST)]
-    lines += ["", f"Finest-level Gauss-Seidel colour pass `{GS_FINEST}`: average "
-              f"{mean(gsd[0]) / 1e3:.1f} us over {len(gsd[0])} launches; "
-              f"{gs[0] / 1e6:.1f} MB fetched + {gs[1] / 1e6:.1f} MB written per launch.", ""]
+    g = max(gg for (n, gg) in dur if n == UP_FINEST) # the finest level's
+    upd = finest(dur[(UP_FINEST, g)])
+    up = (mean(finest(fe[(UP_FINEST, g, "FETCH_SIZE")])) * 1024 * sf,
+          mean(finest(wr[(UP_FINEST, g, "WRITE_SIZE")])) * 1024 * sw)
+    lines += ["", f"Finest-level prolongation and post-smoothing `{UP_FINEST}`: average "
+              f"{mean(upd) / 1e3:.1f} us over {len(upd)} launches; "
+              f"{up[0] / 1e6:.1f} MB fetched + {up[1] / 1e6:.1f} MB written per launch.", ""]
     os.makedirs(os.path.dirname(os.path.abspath(a.md)), exist_ok=True)
     open(a.md, "w").write("\n".join(lines))
-    json.dump({"kernel": GS_FINEST, "kernel_source_sha256_16": kh,
-               "bytes_per_launch": gs[0] + gs[1], "fetch_bytes": gs[0], "write_bytes": gs[1],
-               "fetch_scale": sf, "write_scale": sw, "avg_us_trace": mean(gsd[0]) / 1e3},
+    json.dump({"kernel": UP_FINEST, "kernel_source_sha256_16": kh,
+               "bytes_per_launch": up[0] + up[1], "fetch_bytes": up[0], "write_bytes": up[1],
+               "fetch_scale": sf, "write_scale": sw, "avg_us_trace": mean(upd) / 1e3},
               open(a.traffic, "w"), indent=1)
     print("\n".join(lines))
     if a.plane_md:
@@ -141,19 +144,21 @@ def vcycle_sources_hash() -> str:
 
 def vcycle_traffic(a, fe, wr, sf, sw):
     """HBM bytes of one FP64 preconditioning V-cycle by the counters: the
-    kernels of one cycle as the kernel trace shows it (from a zero-iterate
-    finest-level pass to the next, with no outer-iteration kernel between:
+    kernels of one cycle as the kernel trace shows it (from a finest-level
+    pre-smoothing launch to the next, with no outer-iteration kernel between:
     a cycle of the graph replays that time it), each at its mean FETCH_SIZE
     and WRITE_SIZE per dispatch."""
     c = sqlite3.connect(a.kt)
-    rows = [(short(n), s, g) for n, s, g in
-            c.execute("select name, start, grid_x from kernels order by start")]
-    starts = [i for i, r in enumerate(rows) if r[0] == "k_gs_march2<double, 0, 1>"]
+    rows = [(short(n), s, g, d) for n, s, g, d in
+            c.execute("select name, start, grid_x, duration from kernels order by start")]
+    least = 0.5 * max(r[3] for r in rows if r[0] == "k_vpre_march<double>")
+    starts = [i for i, r in enumerate(rows)
+              if r[0] == "k_vpre_march<double>" and r[3] > least]
     outer = ("k_apply", "k_cg", "k_reduce", "k_cast", "k_dot", "k_copy")
     best = None
     for i0, i1 in zip(starts, starts[1:]):
         cyc = rows[i0:i1]
-        if any(n.startswith(outer) for n, _, _ in cyc):
+        if any(r[0].startswith(outer) for r in cyc):
             continue
         span = (rows[i1][1] - rows[i0][1]) / 1e3
         if best is None or span < best[0]:
@@ -162,7 +167,7 @@ def vcycle_traffic(a, fe, wr, sf, sw):
         raise SystemExit("no bare V-cycle in the kernel trace")
     span, cyc = best
     total = 0.0
-    for n, _, g in cyc:
+    for n, _, g, _ in cyc:
         f = fe.get((n, g, "FETCH_SIZE"))
         w = wr.get((n, g, "WRITE_SIZE"))
         if not f or not w:
@@ -173,7 +178,8 @@ def vcycle_traffic(a, fe, wr, sf, sw):
                    "graph-replayed cycle",
            "bytes_per_cycle": total, "kernels_per_cycle": len(cyc),
            "trace_span_us": span, "fetch_scale": sf, "write_scale": sw,
-           "source_sha256_16": vcycle_sources_hash()}
+           "source_sha256_16": vcycle_sources_hash(),
+           "march_sha256_16": hashlib.sha256(open(MARCH_SRC, "rb").read()).hexdigest()[:16]}
     json.dump(out, open(a.vcycle_traffic, "w"), indent=1)
     print(json.dumps(out, indent=1))
 
@@ -184,7 +190,7 @@ STEP_KERNELS = ("k_divergence", "k_divergence2", "k_correct", "k_line_factor", "
 
 def step_summary(a, dur, fe, wr, sf, sw):
     lines = ["# rocprofv3 summary: projection step and ADI line solves, spherical shell "
-             "192x256x512", "", "Same runs as the Gauss-Seidel summary (bench.py's `project` and "
+             "192x256x512", "", "Same runs as the V-cycle summary (bench.py's `project` and "
              "`lines` forms); commands:", "", "```", a.cmd, "```", "",
              "Largest grid of each kernel, per launch:", "",
              "| kernel | grid (threads) | launches | avg us | fetch MB | write MB |",
@@ -206,7 +212,7 @@ def step_summary(a, dur, fe, wr, sf, sw):
 def plane_summary(a, dur, fe, wr, sf, sw):
     ph = hashlib.sha256(open(PLANE_SRC, "rb").read()).hexdigest()[:16]
     lines = ["# rocprofv3 summary: plane-smoother half-sweep, spherical shell 192x256x512",
-             "", "Same runs as the Gauss-Seidel summary (bench.py's `plane` form, FP64 and "
+             "", "Same runs as the V-cycle summary (bench.py's `plane` form, FP64 and "
              "FP32 cycles); commands:", "", "```", a.cmd, "```", "",
              f"plane kernel source sha256[:16] = `{ph}`", "",
              "Finest level (largest grid of each kernel), per launch:", "",
