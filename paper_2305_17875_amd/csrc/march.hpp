@@ -574,6 +574,11 @@ __device__ __forceinline__ double d_vpost_march(Blk bk, const Geo& g, const Marc
     const unsigned ms = (unsigned)kMRec * ws * (unsigned)(g.nt / 2 + 1);
     const int as = P.a0 - 4, ae = P.a1 + 3; // steps; as is even
     auto plane = [&](int a) { return (unsigned)clampi(a, g.nr - 1) * sr; };
+    // the iterate's, q the parity of a: past an r-wall the nearest plane of that
+    // parity, whose red cells lie where a's do.  The wall's own plane would
+    // give its black cells, which nothing has written: they meet only zero
+    // metrics, but memory may hold NaN there.
+    auto xplane = [&](int a, int q) { return (unsigned)min(max(a, q), g.nr - 2 + q) * sr; };
     const MTab<T> tab = (MTab<T>)(uintptr_t)M;
     unsigned m = ((unsigned)(as - 4 + kMPad) * (unsigned)(g.nt / 2 + 1) + (unsigned)(b0 >> 1)) *
                  ((unsigned)kMRec * ws); // its record at plane a - 4
@@ -599,8 +604,8 @@ __device__ __forceinline__ double d_vpost_march(Blk bk, const Geo& g, const Marc
         for (int n = 0; n < 6; ++n) bB[k][n] = bR[k][n] = T(0);
 #pragma unroll
         for (int n = 0; n < 3; ++n) R0[k][n] = B1[k][n] = R2[k][n] = B3[k][n] = T(0);
-        xn[k][0] = Xi.ld(oj, plane(as) + row(k, k)); // as is even: row k's red parity is k
-        xn[k][1] = Xi.ld(oj, plane(as + 1) + row(k, 1 - k));
+        xn[k][0] = Xi.ld(oj, xplane(as, 0) + row(k, k)); // as is even: row k's red parity is k
+        xn[k][1] = Xi.ld(oj, xplane(as + 1, 1) + row(k, 1 - k));
         xn[k][2] = T(0);
     }
     lde((as >> 1) - 1); // coarse planes I - 1, I, I + 1 of plane as = 2 I: slots 2, 0, 1
@@ -632,7 +637,7 @@ __device__ __forceinline__ double d_vpost_march(Blk bk, const Geo& g, const Marc
             Lw.st(0, 1, R0[0][n0]);
             Lw.st(0, 2, R0[1][n0]);
         }
-        const unsigned p2 = plane(a + 2);
+        const unsigned p2 = xplane(a + 2, Q);
 #pragma unroll
         for (int k = 0; k < 2; ++k) // row k's red parity at even distance: (Q + k) & 1
             xn[k][slot<PH, 3>(-2)] = Xi.ld(oj, p2 + row(k, (Q + k) & 1));

@@ -77,3 +77,28 @@ def test_batch_equals_alone():
             assert np.array_equal(host(x), host(r.p)), g.shape
         finally:
             s.close()
+
+
+@pytest.mark.parametrize("shape", [(80, 96, 144), (64, 40, 464)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_intermediate_iterate_needs_no_black_cells(shape):
+    """The way down writes only the red cells of its iterate, so a solve must
+    not depend on what the black ones hold.  A V-cycle of NaN from a nonzero
+    iterate stores its whole residual (rings that are no row pairs) in the
+    buffer that later holds that iterate; the same solve before and after it
+    gives the same bits."""
+    g = Shell(*shape, radial_stretch=2.0)
+    b = dev(inputs.smoothed_noise(shape, 33)).flatten()
+    s = cps.Solver(g, max_iters=3, stream=torch.cuda.Stream())
+    try:
+        before = s.solve(b)
+        x = host(before.p)
+        nan = torch.full((g.cells,), float("nan"), dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        cps.cps_debug_vcycle(s.h, nan, nan.clone())
+        after = s.solve(b)
+        log("march black cells", shape, before.rel_residual, after.rel_residual)
+        assert after.status == before.status == cps.CPS_E_NOT_CONVERGED
+        assert np.array_equal(host(after.p), x)
+    finally:
+        s.close()
