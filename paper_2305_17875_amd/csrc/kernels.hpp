@@ -2936,6 +2936,14 @@ struct LDesc {
     MarchGrid mg;
 };
 
+// where a level's iterate is after the way up (as xfin of the single solve):
+// the tile path leaves it in xt, the marching path in r
+template <typename T>
+__host__ __device__ inline T* level_result(const LDesc<T>& d)
+{
+    return d.tile ? d.xt : (d.mt ? d.r : d.x);
+}
+
 template <typename T>
 struct PDesc {
     int L, nc, ncol, pad;
@@ -3051,7 +3059,7 @@ __global__ void __launch_bounds__(kBlock) kb_prolong(const BItem* __restrict__ i
     const PDesc<T>& P = pd[it.prob];
     const MarchShape ms = march_shape(P.lv[level + 1].g);
     const LDesc<T>& c = P.lv[level + 1];
-    d_prolong<T, RED>(bk, P.lv[level].g, c.g, ms.bpa, ms.ch, c.tile ? c.xt : c.x, P.lv[level].x);
+    d_prolong<T, RED>(bk, P.lv[level].g, c.g, ms.bpa, ms.ch, level_result(c), P.lv[level].x);
 }
 
 template <typename T>

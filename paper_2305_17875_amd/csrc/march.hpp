@@ -779,7 +779,7 @@ __global__ void __launch_bounds__(kMThreads) kb_vpost_march(const BItem* __restr
     const LDesc<T>& c = pd[it.prob].lv[level + 1];
     d_vpost_march<T>(bk, d.g, d.mg, d.mt, d.b,
                      level == 0 ? d.r : d.x, level == 0 ? d.x : d.r, c.g,
-                     c.tile ? c.xt : (c.mt ? c.r : c.x), sh);
+                     level_result(c), sh);
 }
 
 #undef MSTAGE

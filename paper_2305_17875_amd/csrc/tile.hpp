@@ -467,7 +467,7 @@ __global__ void __launch_bounds__(kTileThreads) kb_vpost_tile(const BItem* __res
     const LDesc<T>& c = pd[it.prob].lv[level + 1];
     // the finest level reads xt and writes x; the others read x, write xt
     d_vpost_tile<T>(bk, d.g, d.G, d.gk, d.b, level == 0 ? d.xt : d.x, level == 0 ? d.x : d.xt,
-                    c.g, c.tile ? c.xt : c.x, sh);
+                    c.g, level_result(c), sh);
 }
 
 // A four-colour Gauss-Seidel sweep (operators with cross terms) of a small

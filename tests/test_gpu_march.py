@@ -102,3 +102,29 @@ def test_intermediate_iterate_needs_no_black_cells(shape):
         assert np.array_equal(host(after.p), x)
     finally:
         s.close()
+
+
+def test_batch_with_a_finest_level_too_large_to_march():
+    """2^28 cells run pass by pass above a level that marches: the batch takes
+    the correction from where that level left it, so two iterations give the
+    bits of the problem alone."""
+    g = Shell(1024, 512, 512, radial_stretch=2.0)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(34)
+    b = torch.randn(g.cells, generator=gen, dtype=torch.float64, device="cuda")
+    log("march batch", g.shape)
+    B = cps.Batch([g], smoother=0, max_iters=2)
+    try:
+        st, p, infos = B.solve([b])
+        x = p[0].clone()
+    finally:
+        B.close()
+    s = cps.Solver(g, precision=1, smoother=0, max_iters=2)
+    try:
+        r = s.solve(b)
+        log("march batch", infos[0].rel_residual, r.rel_residual)
+        assert st == r.status == cps.CPS_E_NOT_CONVERGED
+        assert infos[0].rel_residual == r.rel_residual and torch.equal(x, r.p)
+    finally:
+        s.close()
+        torch.cuda.empty_cache()
