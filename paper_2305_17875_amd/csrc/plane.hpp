@@ -541,6 +541,22 @@ __host__ __device__ inline TriLaunch tri_launch(const Geo& g, int parity, int wa
     return t;
 }
 
+// The wavefronts [lo, hi) of a block that hold the line of wavefront wv: it
+// takes the values of the chunks below from [lo, wv), of those above from
+// (wv, hi).  Wavefronts past a block's whole groups (a batched block is of one
+// size whatever its lines need) hold no line and take none.
+struct TriLine {
+    int lo, hi;
+    bool live;
+};
+
+__host__ __device__ inline TriLine tri_line(const TriLaunch& t, int wv)
+{
+    const int grp = wv / t.nw;
+    if (grp >= t.gpb) return TriLine{wv, wv + 1, false};
+    return TriLine{grp * t.nw, (grp + 1) * t.nw, true};
+}
+
 template <typename T>
 struct TriLds {
     Vec2<T> f[kTriWaves][64], b[kTriWaves][64]; // a chunk's end value and its factor
@@ -560,9 +576,10 @@ __device__ __forceinline__ void d_tri_chunk(unsigned blk, const TriLaunch& tl, c
     const int rows = (g.nt - parity + 1) / 2, nh = g.nh, nr = g.nr;
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int lane = (int)threadIdx.x & 63;
-    const int grp = wv / tl.nw, c = wv - grp * tl.nw;
+    const TriLine ln = tri_line(tl, wv);
+    const int grp = wv / tl.nw, c = wv - ln.lo; // the line's chunk c
     const unsigned u = (blk * (unsigned)tl.gpb + (unsigned)grp) * 64u + (unsigned)lane;
-    const bool live = grp < tl.gpb && u < (unsigned)tl.lanes;
+    const bool live = ln.live && u < (unsigned)tl.lanes;
     const unsigned t = live ? u >> 1 : 0u; // line
     const unsigned bl = INLDS ? ldsrow : t / (unsigned)nh;
     const unsigned m = INLDS ? t : t - bl * (unsigned)nh;
@@ -609,8 +626,8 @@ __device__ __forceinline__ void d_tri_chunk(unsigned blk, const TriLaunch& tl, c
         }
         sh.f[wv][lane] = v;
         __syncthreads();
-        for (int w = 0; w < c; ++w) {
-            const Vec2<T> q = sh.f[wv - c + w][lane];
+        for (int w = ln.lo; w < wv; ++w) {
+            const Vec2<T> q = sh.f[w][lane];
             below = fma_t(q.y, below, q.x);
         }
     }
@@ -631,8 +648,8 @@ __device__ __forceinline__ void d_tri_chunk(unsigned blk, const TriLaunch& tl, c
         }
         sh.b[wv][lane] = v;
         __syncthreads();
-        for (int w = tl.nw - 1; w > c; --w) {
-            const Vec2<T> q = sh.b[wv - c + w][lane];
+        for (int w = ln.hi - 1; w > wv; --w) {
+            const Vec2<T> q = sh.b[w][lane];
             above = fma_t(q.y, above, q.x);
         }
     }

@@ -174,3 +174,24 @@ def test_batch_equals_alone_near_fp64_reach():
             r.rel_residual)
         assert info.iterations == r.iterations and info.rel_residual == r.rel_residual, i
         assert np.array_equal(x, xa), (i, np.abs(x - xa).max())
+
+
+@pytest.mark.parametrize("n_r", [48, 80, 96, 112])
+def test_plane_batch_with_wavefronts_that_hold_no_line(n_r):
+    """Lines of 3, 5, 6 and 7 wavefronts in batched blocks of 16, on levels
+    of three launches a half-sweep and of one, with and without cross terms: the
+    idle wavefronts change nothing, each problem has the bits it gets alone."""
+    grids = [Shell(n_r, 16, 64), Shell(n_r, 16, 32, map=MAP_OBLATE, flattening=0.1)]
+    rhs = [rhs_of(50 + i, g) for i, g in enumerate(grids)]
+    log("plane batch", n_r)
+    B = cps.Batch(grids, smoother=1)
+    try:
+        st, p, infos = B.solve([dev(b).flatten() for b in rhs])
+        xs = [host(t).reshape(g.shape) for t, g in zip(p, grids)]
+    finally:
+        B.close()
+    assert st == cps.CPS_OK
+    for i, (g, b, x, info) in enumerate(zip(grids, rhs, xs, infos)):
+        xa, ra = alone(g, b, smoother=1)
+        assert info.iterations == ra.iterations, i
+        assert np.array_equal(x, xa), (i, np.abs(x - xa).max())

@@ -37,3 +37,10 @@ def test_batched_coarse_correction(rules):
     for name in ("kernels.hpp", "tile.hpp", "march.hpp"):
         text = open(os.path.join(CSRC, name)).read()
         assert len(re.findall(r"\.tile \?", text)) == (1 if name == "kernels.hpp" else 0), name
+
+
+def test_elimination_reads_within_its_block(rules):
+    """In the chunked r-line elimination a wavefront reads only the values of
+    its own line's wavefronts, and one that holds no line (a batched block of 16
+    wavefronts whose lines need 3, 5, 6, ...) reads none, for every line length."""
+    rules("elimination_slots")
