@@ -101,13 +101,15 @@ size_t estimate_bytes(const cps_grid& g, const cps_opts& o)
         s += 9 * gk * 8;
         if (mixed) s += 9 * gk * 4 + n * 4 * (l + 1 < L ? 3 : 2);
         else s += n * 8 * ((l > 0 ? 2 : 0) + (l + 1 < L ? 1 : 0));
-        // the tile path's second iterate (small levels, point smoother)
-        if (l + 1 < L && tile_fits(make_geo(dims[l][0], dims[l][1], dims[l][2]), l, mixed))
-            s += n * (mixed ? 4 : 8);
-        // the marching path's metrics table (large levels)
-        if (l + 1 < L && n > (size_t)kMarchCells)
-            s += (size_t)march_table_words(make_geo(dims[l][0], dims[l][1], dims[l][2])) *
-                 (mixed ? 4 : 8);
+    }
+    // the point smoother's: the tile path's second iterate (small levels), the
+    // marching path's metrics table (large ones); 7-point operators only
+    size_t point = 0;
+    for (int l = 0; axi && l + 1 < L; ++l) {
+        const Geo q = make_geo(dims[l][0], dims[l][1], dims[l][2]);
+        const size_t w = mixed ? 4 : 8;
+        if (tile_fits(q, l, mixed)) point += 2 * (size_t)q.P * w;
+        else if (march_fits(q)) point += (size_t)march_table_words(q) * w;
     }
     const size_t n0 = (size_t)g.n_r * g.n_theta * g.n_phi;
     const size_t nc = (size_t)dims[L - 1][0] * dims[L - 1][1] * dims[L - 1][2];
@@ -117,14 +119,17 @@ size_t estimate_bytes(const cps_grid& g, const cps_opts& o)
         const int nh = dims[l][2] / 2;
         plane_dims = plane_dims && nh >= 2 && nh <= kPlaneLds && (nh & (nh - 1)) == 0;
     }
-    if (o.smoother == 1 || (o.smoother == 2 && plane_dims)) {
-        // spectra of one parity, pivots of every smoothed level, tables
-        const size_t w = mixed ? 4 : 8;
-        s += (size_t)dims[0][0] * ((dims[0][1] + 1) / 2) * (dims[0][2] / 2 + 1) * 2 * w +
-             (size_t)L * (2 * dims[0][2] + 8) * 8 * 2;
-        for (int l = 0; l + 1 < L; ++l)
-            s += (size_t)dims[l][0] * dims[l][1] * (dims[l][2] / 2 + 3) * w;
-    }
+    // the plane smoother's: spectra of one parity, pivots of every smoothed
+    // level, tables
+    const size_t w = mixed ? 4 : 8;
+    size_t plane = (size_t)dims[0][0] * ((dims[0][1] + 1) / 2) * (dims[0][2] / 2 + 1) * 2 * w +
+                   (size_t)L * (2 * dims[0][2] + 8) * 8 * 2;
+    for (int l = 0; l + 1 < L; ++l)
+        plane += (size_t)dims[l][0] * dims[l][1] * (dims[l][2] / 2 + 3) * w;
+    // one of the two (automatic: the map decides, where the rings allow both)
+    if (o.smoother == 1) s += plane;
+    else if (o.smoother == 2 && plane_dims) s += std::max(plane, point);
+    else s += point;
     s += (2 * std::max<size_t>(n0 / kBlock + 1, kMaxGrid) + 64 + S_COUNT) * 8 +
          nc * nc * 8 * 4 + nc * kGJ * 8 * 3 + (2 * nc + 1) * 4;
     return s;

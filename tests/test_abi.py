@@ -1,6 +1,7 @@
 """Host-side checks of the C ABI: the library loads without a GPU, exports
 every function that include/cps.h declares, and the ctypes structures match
 the C layout (sizes and offsets printed by a gcc-compiled probe)."""
+import math
 import os
 import re
 import subprocess
@@ -114,3 +115,37 @@ def test_service_report_layout_and_footprint(tmp_path):
     assert fo > f[2]  # BiCGStab's extra vectors
     with pytest.raises(cps.CpsError, match="coarsest"):
         cps.cps_service_footprint(cps.make_grid(Shell(15, 16, 32)), opts)
+
+
+@pytest.mark.parametrize("shape", [(32, 32, 64), (64, 64, 64), (96, 128, 256), (512, 512, 32)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_footprint_counts_one_smoother(shape):
+    """A hierarchy holds the buffers of one smoother: the plane one's spectra
+    and pivots, or the point one's (a second iterate of a small level, the
+    metrics table of a large one; 7-point operators only), never both."""
+    if not os.path.exists(cps.LIB_PATH):
+        pytest.skip("libcps.so not built")
+    import oracle as O
+    from paper_2305_17875_amd.inputs import Shell, MAP_TRIAXIAL
+    levels = O.level_plan(*shape)
+    for precision, word in ((0, 8), (1, 4)):
+        f = [cps.cps_service_footprint(cps.make_grid(Shell(*shape)),
+                                       cps.cps_opts(precision, 200, 1, 0, 0, k, None))
+             for k in (0, 1, 2)]
+        nr, nt, np_ = shape
+        plane = nr * ((nt + 1) // 2) * (np_ // 2 + 1) * 2 * word + len(levels) * (2 * np_ + 8) * 16
+        plane += sum(a * b * (c // 2 + 3) for a, b, c in levels[:-1]) * word
+        point = 0
+        for k, (a, b, c) in enumerate(levels[:-1]):
+            n = a * b * c
+            most = 1 << 19 if precision else (1 << 18 if k and (c // 2) % 64 else 1 << 16)
+            point += n if n <= most else (8 * (a + 20) * (b // 2 + 1) if n > 1 << 20 else 0)
+        point *= word
+        assert f[1] - f[0] == plane - point and f[2] == max(f[0], f[1]), (precision, f)
+    t = Shell(*shape, map=MAP_TRIAXIAL, flattening=0.1, skew=0.1)
+    n0, nc = math.prod(shape), math.prod(levels[-1])
+    got = cps.cps_service_footprint(cps.make_grid(t), cps.cps_opts(0, 200, 1, 0, 0, 0, None))
+    # metrics, level vectors, nine finest-level vectors, reductions, coarsest inverse
+    cells = sum(map(math.prod, levels))
+    want = 9 * cells * 8 + (3 * cells - 2 * n0 - nc) * 8 + 9 * n0 * 8
+    assert want < got <= want + (2 * max(n0 // 256 + 1, 4096) + 256) * 8 + nc * (nc + 1) * 40
