@@ -52,7 +52,6 @@ TILE_SRC = os.path.join(ROOT, "paper_2305_17875_amd", "csrc", "tile.hpp")
 KNAMES = ["gs_pass", "residual", "apply", "restrict", "prolong", "vcycle", "divergence",
           "correct", "down", "up"]
 UP_KERNEL = "k_vpost_march<double>"
-MARCH_CELLS = 1 << 20  # levels of more cells take the marching path
 
 
 def log(*a):
@@ -149,16 +148,23 @@ def march_words():
     return 1.0 + 0.5 + 0.125, 0.5 + 0.125 + 1.0 + 1.0
 
 
+def marches(shape):
+    """Whether a level of the 7-point hierarchy takes the marching path: more
+    than 2^20 and fewer than 2^28 cells, even in r, theta and phi pairs."""
+    nr, nt, np_ = shape
+    return 1 << 20 < nr * nt * np_ < 1 << 28 and not (nr % 2 or nt % 2 or np_ % 4)
+
+
 def vcycle_bytes_marching(levels, word):
-    """vcycle_bytes with the levels of more than MARCH_CELLS cells at the
-    bytes of their two launches (and the metrics table of each once)."""
+    """What a cycle's launches have to move: vcycle_bytes with the levels that
+    march at the bytes of their two launches (and the metrics table, four
+    words per (r, theta), once each)."""
     whole = vcycle_bytes(levels, word, fused=True, red_prolong=True)
-    for k, lv in enumerate(levels[:-1]):
-        n = lv[0] * lv[1] * lv[2]
-        if n <= MARCH_CELLS:
+    for lv, c in zip(levels, levels[1:]):
+        if not marches(lv):
             continue
-        passes = vcycle_bytes([lv, levels[k + 1]], word, fused=True, red_prolong=True)
-        ncc = levels[k + 1][0] * levels[k + 1][1] * levels[k + 1][2]
+        n, ncc = lv[0] * lv[1] * lv[2], c[0] * c[1] * c[2]
+        passes = vcycle_bytes([lv, c], word, fused=True, red_prolong=True)
         passes -= ncc * ncc * 8 + 2 * ncc * word
         whole += int(round((sum(march_words()) * n + 2 * 4 * lv[0] * lv[1]) * word)) - passes
     return whole
@@ -166,17 +172,30 @@ def vcycle_bytes_marching(levels, word):
 
 def plane_half_sweep_bytes(shape, word):
     """Algorithmic HBM bytes of one zebra half-sweep of the plane smoother
-    (the theta rows of one parity), per kernel with no cross-kernel fusion:
-    the forward transform reads b of the relaxed rows and x of the other
-    parity and writes the spectra; the r-line elimination reads and writes
-    the spectra twice (down and up) and reads the inverse pivots twice (the
-    streaming form; the chunked one moves them once, so the rate of these
-    bytes reads higher than the memory's); the inverse transform reads the spectra and writes x of the relaxed rows."""
+    (the theta rows of one parity), per kernel with no cross-kernel fusion, for
+    lines that the elimination streams (n_r > 256): the forward transform reads
+    b of the relaxed rows and x of the other parity and writes the spectra; the
+    r-line elimination reads and writes the spectra twice (down and up) and
+    reads the inverse pivots twice; the inverse transform reads the spectra and
+    writes x of the relaxed rows."""
     nr, nt, np_ = shape
     half = nr * nt * np_ // 2
     spec = nr * (nt // 2) * (np_ // 2 + 1) * 2  # words: (n_phi/2 + 1) complex per ring
     piv = spec // 2
     return (2 * half + spec + 4 * spec + 2 * piv + spec + half) * word
+
+
+def half_sweep_bytes(shape, word):
+    """plane_half_sweep_bytes for the elimination that a line takes: up to 256
+    cells in chunks, which move the spectra (n_phi reals a ring, modes 0 and
+    n_phi / 2 sharing a slot) in and out once, and n_phi / 2 + 1 pivots and two
+    off-diagonals a ring once."""
+    nr, nt, np_ = shape
+    if nr > 256:
+        return plane_half_sweep_bytes(shape, word)
+    rings = nr * (nt // 2)
+    half = rings * np_
+    return (2 * half + half + 2 * half + rings * (np_ // 2 + 3) + half + half) * word
 
 
 PROF_STEPS = 2
@@ -265,11 +284,11 @@ def kernel_table(prof, steps):
     return out
 
 
-def vcycle_rate(prof, levels, word, steps, graph_us=None, traffic=None):
-    """HBM rate of the preconditioning V-cycle: the byte model of
-    vcycle_bytes over the time of one cycle.  graph_us: the cycle replayed
-    from a hipGraph as the solve runs it (cps_time_vcycle), the rate's
-    time; the span of each cycle measured with HIP events in solves that
+def vcycle_rate(prof, levels, word, steps, graph_us=None, traffic=None, moved=None):
+    """HBM rate of the preconditioning V-cycle: `moved` bytes (by default
+    those of vcycle_bytes, a launch a pass) over the time of one cycle.
+    graph_us: the cycle replayed from a hipGraph as the solve runs it
+    (cps_time_vcycle), the rate's time; the span of each cycle measured with HIP events in solves that
     launch every kernel from the host (profiling) is reported beside it
     (eager_*), and is the rate's time when graph_us is None."""
     ms, cnt = prof[KNAMES.index("vcycle")]
@@ -277,14 +296,8 @@ def vcycle_rate(prof, levels, word, steps, graph_us=None, traffic=None):
         return None
     eager = ms / cnt * 1e-3
     t = graph_us * 1e-6 if graph_us else eager
-    b = vcycle_bytes(levels, word, fused=True, red_prolong=True)
-    # what the cycle has to move with its large levels in two launches: the
-    # rate against the memory's peak (bytes_per_cycle counts every pass's own
-    # bytes, of which the marching path moves a part only)
-    bm = vcycle_bytes_marching(levels, word)
-    out = {"marching_bytes_per_cycle": bm, "marching_achieved_GBs": bm / t / 1e9,
-           "marching_frac_of_peak": bm / t / 1e9 / HBM_PEAK_GBS,
-           "bytes_per_cycle": b, "avg_us": t * 1e6, "achieved_GBs": b / t / 1e9,
+    b = moved or vcycle_bytes(levels, word, fused=True, red_prolong=True)
+    out = {"bytes_per_cycle": b, "avg_us": t * 1e6, "achieved_GBs": b / t / 1e9,
            "frac_of_peak": b / t / 1e9 / HBM_PEAK_GBS, "cycles_per_step": cnt / steps,
            "timing": ("hipGraph replay of 10 cycles, 5 launches between events "
                       "(cps_time_vcycle)") if graph_us else "HIP events around each cycle, "
@@ -328,7 +341,7 @@ def plane_form(cps, torch, g, rhs, x64, steps, warmup, answers):
     """The same solve with the zebra (r, phi)-plane smoother in place of
     point red-black Gauss-Seidel (cps_opts.smoother = 1): FP64 and FP32
     cycles, each with its half-sweep rate against the byte model of
-    plane_half_sweep_bytes."""
+    half_sweep_bytes."""
     out = {"smoother": "zebra (r,phi)-plane block Gauss-Seidel: FFT along phi, "
                        "Thomas along r per mode; V(2,2), PCG"}
     for precision, key, word in ((0, "fp64", 8), (1, "mixed", 4)):
@@ -337,7 +350,7 @@ def plane_form(cps, torch, g, rhs, x64, steps, warmup, answers):
         answers[("plane", key)] = f["host_p"]
         hs_ms, hs_n = f["timed_pass"]  # HIP events over the timed region
         hs_s = hs_ms / max(hs_n, 1) * 1e-3
-        hb = plane_half_sweep_bytes(g.shape, word)
+        hb = half_sweep_bytes(g.shape, word)
         err = float(torch.linalg.norm(f["p"] - x64) / torch.linalg.norm(x64))
         out[key] = {"value": g.cells / f["sec"], "unit": "unknowns/s",
                     "ms_per_step": f["sec"] * 1e3, "setup_ms": f["setup_s"] * 1e3,
@@ -933,7 +946,8 @@ def main():
                      "frac_of_copy": achieved / copy_gbs if copy_gbs else None},
         "kernels_fp64": kernel_table(f64["prof"], f64["prof_steps"]),
         "vcycle_fp64": vcycle_rate(f64["prof"], s64.levels, 8, f64["prof_steps"],
-                                   f64["vcycle_graph_us"], vcycle_traffic()),
+                                   f64["vcycle_graph_us"], vcycle_traffic(),
+                                   vcycle_bytes_marching(s64.levels, 8)),
     }
     x64 = f64["p"]
     answers = {("fp64",): f64["host_p"]}  # GPU answers, compared with the oracle's exact one
@@ -948,7 +962,8 @@ def main():
                          "rel_diff_vs_fp64": err, "dtype": "f32 V-cycles, f64 outer",
                          "kernels": kernel_table(mx["prof"], mx["prof_steps"]),
                          "vcycle": vcycle_rate(mx["prof"], mx["solver"].levels, 4, mx["prof_steps"],
-                                               mx["vcycle_graph_us"])}
+                                               mx["vcycle_graph_us"], moved=vcycle_bytes_marching(
+                                                   mx["solver"].levels, 4))}
         answers[("mixed",)] = mx["host_p"]
         mx["solver"].close()
         del mx

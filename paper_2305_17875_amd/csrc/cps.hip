@@ -864,12 +864,14 @@ long long vcycle(cps_handle* h, const T* b0, T* x0, bool x0_zero = false, bool d
 }
 
 // Partial sums that every block of the consuming launch adds up itself, and the
-// most blocks that do so: 8 KB a block from L2 at most, under 1 us, where the
-// launch for a sum takes 2.4 to 4.6 us (32^3: three sums of 64 to 128 parts an
-// iteration; 80 x 96 x 144: 180 and 1080).
+// most blocks that do so: 16 KB a block from L2 at most.  With 1080 parts
+// (80 x 96 x 144) the step takes 0.6 us longer than without the sum, with 1920
+// (160 x 128 x 96) 1.4 us, where the launch for a sum takes 2.4 to 4.6 us.
 constexpr long long kFoldParts = 2048;
 constexpr int kFoldGrid = 1024;
-// the most cells of a problem whose iterations are launched ahead
+// The most cells of a problem whose iterations are launched ahead: the 12 to
+// 14 us saved are a fifth of an iteration of 32^3 and a tenth of one of
+// 1.1 M cells (80 x 96 x 144), and larger problems wait
 constexpr long long kAheadCells = 1LL << 21;
 
 // out = M^-1 in : one V-cycle from zero, FP64 or FP32 inside (scaled by
@@ -1635,6 +1637,8 @@ cps_status solve(cps_handle* h, const double* rhs, double* p_out, double tol, cp
             // the step launched ahead leaves the iterate and the residual as
             // they are (S_STOP).  That costs one iteration's time a solve, so
             // large problems, and the plane smoother's few iterations, wait.
+            // So do row-pair rings: their direction kernel updates the iterate
+            // two steps late, which the gate of the step does not cover.
             double stop_rr = 0.0;
             const bool ahead = !fused && h->opts.smoother == 0 && n <= kAheadCells &&
                                !h->opts.eager && !h->prof && h->stream &&

@@ -113,17 +113,6 @@ struct Delta {
     __device__ __forceinline__ T operator()(long long i) const { return i == j ? T(1) : T(0); }
 };
 
-// (A x) at cell (a, b, c = 2j + s) as the sum over directions of (flux
-// through the high face) - (flux through the low face), and
-// D = -(sum of the six G_dd).  The flux through a face in direction d is
-//   G_dd (x_hi - x_lo) + sum_{q != d} G_dq/4 (x_hi+q + x_lo+q - x_hi-q - x_lo-q),
-// eq. (PC_term1)-(PC_term3) generalised to all nine terms; reads that leave
-// the domain in r or theta mirror onto the wall cell, phi wraps.
-// OFFDIAG: return instead S = (A x)_c - D x_c, the sum over the neighbours
-// (including a wall-mirrored read of the cell itself in a cross term), so a
-// Gauss-Seidel update x_c = (b_c - S) / D never loads the old x_c.  The flux
-// form (differences first) is kept for residuals, whose value is small next
-// to D x_c near convergence.
 // The metrics of a cell's six faces (low and high of each direction; pq: the
 // cross term of face p in direction q), from the metric indices of its low
 // faces (ci) and of its r, theta and phi high ones; zero on the high walls.
@@ -209,6 +198,17 @@ __device__ __forceinline__ T stencil_sum(const FaceMetrics<T>& m, const Acc& X, 
     return acc;
 }
 
+// (A x) at cell (a, b, c = 2j + s) as the sum over directions of (flux
+// through the high face) - (flux through the low face), and
+// D = -(sum of the six G_dd).  The flux through a face in direction d is
+//   G_dd (x_hi - x_lo) + sum_{q != d} G_dq/4 (x_hi+q + x_lo+q - x_hi-q - x_lo-q),
+// eq. (PC_term1)-(PC_term3) generalised to all nine terms; reads that leave
+// the domain in r or theta mirror onto the wall cell, phi wraps.
+// OFFDIAG: return instead S = (A x)_c - D x_c, the sum over the neighbours
+// (including a wall-mirrored read of the cell itself in a cross term), so a
+// Gauss-Seidel update x_c = (b_c - S) / D never loads the old x_c.  The flux
+// form (differences first) is kept for residuals, whose value is small next
+// to D x_c near convergence.
 template <typename T, int MODE, bool AXI, bool OFFDIAG = false, typename Acc>
 __device__ __forceinline__ T apply_cell(const Geo& g, const T* __restrict__ G, long long gk,
                                         const Acc& X, int a, int b, int s, int j, T& D)

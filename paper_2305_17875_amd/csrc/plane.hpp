@@ -874,7 +874,9 @@ __device__ __forceinline__ void d_plane_row(unsigned bi, PlaneRowLds<T>& sh, con
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const int m = tr + i * tpr;
-            if (m < nh) X[i] = ring_mode<T>(m, A[sw<T, kSmallRing>(m)], A[sw<T, kSmallRing>(m == 0 ? 0 : nh - m)], sh.twN[m]);
+            if (m < nh)
+                X[i] = ring_mode<T>(m, A[sw<T, kSmallRing>(m)],
+                                    A[sw<T, kSmallRing>(m == 0 ? 0 : nh - m)], sh.twN[m]);
         }
         wave_sync();
 #pragma unroll
@@ -899,7 +901,9 @@ __device__ __forceinline__ void d_plane_row(unsigned bi, PlaneRowLds<T>& sh, con
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const int m = tr + i * tpr;
-            if (m < nh) Z[i] = ring_value<T>(m, A[sw<T, kSmallRing>(m)], A[sw<T, kSmallRing>(m == 0 ? 0 : nh - m)], sh.twN[m]);
+            if (m < nh)
+                Z[i] = ring_value<T>(m, A[sw<T, kSmallRing>(m)],
+                                     A[sw<T, kSmallRing>(m == 0 ? 0 : nh - m)], sh.twN[m]);
         }
         wave_sync();
 #pragma unroll

@@ -48,8 +48,12 @@ constexpr int kCoarseR = kTile / 2 + 6;       // coarse correction box of post
 // up to 64 K cells (24 x 32 x 64: 15 us against 46), and coarse levels whose
 // rows are not whole wavefronts, which the per-kernel passes take a cell a
 // thread, up to 256 K (40 x 48 x 72: 21 us against 45; 20 x 24 x 36: 15
-// against 45).  The finest level keeps the per-kernel passes above 64 K: their
-// profiling classes time them one by one.
+// against 45).  The other FP64 levels above 64 K keep the passes although
+// tiles are faster there too up to 512 K (whole cycles, passes / tiles:
+// finest level 16 x 32 x 160 58 / 37 us, 40 x 48 x 72 66 / 48, 48 x 64 x 128
+// 75 / 60, 64 x 64 x 128 77 / 67; as the level below 96 x 128 x 256
+// 145 / 127): the profiling classes of a finest level of that size time its
+// passes one by one, and the coarse limit is that of the finest level.
 constexpr long long kTileMaxCells = 1LL << 16;
 constexpr long long kTileMaxRagged = 1LL << 18;
 constexpr long long kTileMaxCells32 = 1LL << 19;

@@ -154,3 +154,44 @@ def test_vcycle_traffic_follows_the_kernel_sources(bench, tmp_path, monkeypatch)
     assert bench.vcycle_traffic() is None
     f.unlink()
     assert bench.vcycle_traffic() is None
+
+
+def test_two_launch_levels_move_each_field_once(bench):
+    """A marching level: b in, red x and coarse b out (1 + 1/2 + 1/8 words a cell)
+    on the way down, red x, coarse correction and b in, x out (1/2 + 1/8 + 1 + 1)
+    on the way up, four table words per (r, theta) each way; other levels as
+    vcycle_bytes counts them.  Paper scale, by hand: two levels march, 48 x 64 x
+    128 forms the red residual apart (16.25 words less the red prolongation's
+    one), the two below it the whole one."""
+    assert bench.march_words() == (1.625, 2.625)
+    levels = [PAPER_SCALE, (96, 128, 256), (48, 64, 128), (24, 32, 64), (12, 16, 32), (6, 8, 16)]
+    words = 4.25 * (25_165_824 + 3_145_728) + 8 * (192 * 256 + 96 * 128)
+    words += 15.25 * 393_216 + 27 * 48 * 64 + 16.75 * 49_152 + 27 * 24 * 32
+    words += 16.75 * 6_144 + 27 * 12 * 16 + 2 * 768
+    assert bench.vcycle_bytes_marching(levels, 8) == int(words) * 8 + 768 * 768 * 8
+    assert bench.vcycle_bytes_marching(levels, 4) == int(words) * 4 + 768 * 768 * 8
+    assert bench.vcycle_bytes_marching(levels[2:], 8) == \
+        bench.vcycle_bytes(levels[2:], 8, fused=True, red_prolong=True)
+
+
+def test_marching_levels(bench):
+    """More than 2^20 and fewer than 2^28 cells; even counts in r and theta, an
+    even number of phi pairs."""
+    assert bench.marches(PAPER_SCALE) and bench.marches((80, 96, 144))
+    assert not bench.marches((64, 128, 128)) and bench.marches((66, 128, 128))  # 2^20, more
+    assert bench.marches((512, 512, 1020)) and not bench.marches((512, 512, 1024))  # 2^28
+    assert not bench.marches((81, 96, 144)) and not bench.marches((80, 97, 144))
+    assert not bench.marches((80, 96, 146))
+
+
+def test_half_sweep_counts_the_chunked_elimination(bench):
+    """Lines of up to 256 cells: b and x in, spectra (n_phi reals a ring) out;
+    spectra in and out and pivots and off-diagonals in once; spectra in, x out.
+    Longer lines: the streaming form's bytes."""
+    nr, nt, np_ = 4, 6, 16
+    rings = nr * (nt // 2)
+    words = 2 * rings * np_ + rings * np_ + 2 * rings * np_ + rings * (np_ // 2 + 1 + 2) + \
+        2 * rings * np_
+    assert bench.half_sweep_bytes((nr, nt, np_), 8) == words * 8
+    assert bench.half_sweep_bytes(PAPER_SCALE, 8) == 755_564_544
+    assert bench.half_sweep_bytes((257, 6, 16), 4) == bench.plane_half_sweep_bytes((257, 6, 16), 4)
