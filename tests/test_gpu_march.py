@@ -128,3 +128,25 @@ def test_batch_with_a_finest_level_too_large_to_march():
     finally:
         s.close()
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_a_field_near_the_byte_limit(precision):
+    """512 x 960 x 512 cells, 1.9 GiB an FP64 field of the 2 GiB that the
+    marching path addresses: the solve converges, and the residual of its
+    answer, which other kernels form, meets the tolerance."""
+    g = Shell(512, 960, 512, radial_stretch=2.0)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(35)
+    b = torch.randn(g.cells, generator=gen, dtype=torch.float64, device="cuda")
+    b -= b.mean()
+    s = cps.Solver(g, precision=precision, max_iters=200)
+    try:
+        r = s.solve(b, tol=1e-8)
+        log("march byte limit", precision, r.status, r.iterations, r.rel_residual)
+        assert r.status == cps.CPS_OK and r.rel_residual <= 1e-8
+        p = r.p.view(g.shape)
+        assert bool(torch.isfinite(p).all()) and abs(float(p.mean())) <= 1e-12 * float(p.abs().max())
+    finally:
+        s.close()
+        torch.cuda.empty_cache()
